@@ -47,8 +47,9 @@ struct InstallArgs {
   NoallocScratch* s;   // the device's scratch array
   int32_t first;       // first table position this launch writes
   int32_t n;           // table positions this launch writes (<= kInstallTables)
-  int32_t clear;       // 1: also zero counters [0, n_counters), the ticket and the status word
+  int32_t clear;       // 1: also zero the n_counters slice counters, the ticket and the status word
   int32_t n_counters;
+  int32_t counter_shift;
   TabMeta meta[kInstallTables];
   const void* tables[kInstallTables];
   int32_t tperm[kInstallTables];
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(256) void install_kernel(const InstallArgs a) {
     a.s->tperm[a.first + i0] = a.tperm[i0];
   }
   if (a.clear) {
-    for (int64_t k = i0; k < a.n_counters; k += stride) a.s->counters[k] = 0u;
+    for (int64_t k = i0; k < a.n_counters; k += stride) a.s->counters[k << a.counter_shift] = 0u;
     if (i0 < 4) a.s->status[i0] = (i0 & 1) ? 0x7fffffff : 0;
     if (i0 < 2) a.s->ticket[i0] = 0u;
   }
@@ -196,6 +197,7 @@ extern "C" int ebag_a2a_forward_noalloc(int32_t num_tables, const int64_t* rows_
   ps.d_meta = s->meta;
   ps.d_tperm = s->tperm;
   ps.d_counters = s->counters;
+  ps.counter_shift = counter_shift_for(n_flags, EBAG_NOALLOC_MAX_FLAGS, o.slice_granule == 1);
   ps.d_status = s->status;
   ps.d_trace_release = nullptr;
   ps.d_ticket = s->ticket;
@@ -222,6 +224,7 @@ extern "C" int ebag_a2a_forward_noalloc(int32_t num_tables, const int64_t* rows_
     ia.n = num_tables - first < kInstallTables ? num_tables - first : kInstallTables;
     ia.clear = first == 0;
     ia.n_counters = ia.clear ? (int32_t)n_flags : 0;
+    ia.counter_shift = ps.counter_shift;
     for (int32_t i = 0; i < ia.n; ++i) {
       ia.meta[i] = meta[first + i];
       ia.tables[i] = tables[first + i];

@@ -50,6 +50,8 @@ int hip_fail(hipError_t e, const char* what) {
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
+constexpr int64_t kMaxCounterWords = (int64_t)1 << 24;  // spread slice counters: at most 64 MiB, or packed
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 int log2_exact(int v) {
@@ -101,6 +103,7 @@ struct ebag_a2a_plan {
   InFlight fwd, bwd, dlv;
   int64_t max_chunks = 0;
   int64_t max_flags = 0;   // max_chunks, times T with per-table slices
+  int32_t counter_shift = 0;  // PoolArgs::counter_shift
   // device memory
   TabMeta* d_meta = nullptr;
   int32_t* d_tperm = nullptr;
@@ -294,6 +297,7 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->weights = weights;
   a->out = out;
   a->counters = s.d_counters;
+  a->counter_shift = s.counter_shift;
   a->flags = flags;
   a->status = s.d_status;
   a->trace_release = o.trace ? s.d_trace_release : nullptr;
@@ -359,6 +363,7 @@ PoolSetup setup_of(const ebag_a2a_plan* h) {
   s.d_meta = h->d_meta;
   s.d_tperm = h->d_tperm;
   s.d_counters = h->d_counters;
+  s.counter_shift = h->counter_shift;
   s.d_status = h->d_status;
   s.d_trace_release = h->d_trace_release;
   s.d_ticket = h->d_ticket;
@@ -451,6 +456,7 @@ int ebag_a2a_create(ebag_a2a_t* out, int32_t num_tables, const int64_t* rows_per
   h->host_tables.assign(num_tables, nullptr);
   h->max_chunks = (max_batch + chunk_samples - 1) / chunk_samples;
   h->max_flags = h->max_chunks * (o.slice_granule == 1 ? num_tables : 1);
+  h->counter_shift = counter_shift_for(h->max_flags, kMaxCounterWords, o.slice_granule == 1);
 
 #define CREATE_TRY(call, what)                                                             \
   do {                                                                                     \
@@ -480,8 +486,8 @@ int ebag_a2a_create(ebag_a2a_t* out, int32_t num_tables, const int64_t* rows_per
   CREATE_TRY(hipMalloc((void**)&h->d_tperm, sizeof(int32_t) * num_tables), "alloc table order");
   CREATE_TRY(hipMemcpy(h->d_tperm, tperm.data(), sizeof(int32_t) * num_tables, hipMemcpyHostToDevice), "upload order");
   CREATE_TRY(hipMalloc((void**)&h->d_tables, sizeof(void*) * num_tables), "alloc table pointers");
-  CREATE_TRY(hipMalloc((void**)&h->d_counters, sizeof(uint32_t) * h->max_flags), "alloc slice counters");
-  CREATE_TRY(hipMemset(h->d_counters, 0, sizeof(uint32_t) * h->max_flags), "zero slice counters");
+  CREATE_TRY(hipMalloc((void**)&h->d_counters, sizeof(uint32_t) * (h->max_flags << h->counter_shift)), "alloc slice counters");
+  CREATE_TRY(hipMemset(h->d_counters, 0, sizeof(uint32_t) * (h->max_flags << h->counter_shift)), "zero slice counters");
   CREATE_TRY(hipMalloc((void**)&h->d_scratch, sizeof(float) * (size_t)max_batch * (size_t)sum_dim), "alloc scratch");
   CREATE_TRY(hipMalloc((void**)&h->d_value_base, sizeof(int64_t) * (num_tables + 1)), "alloc value bases");
   CREATE_TRY(hipMalloc((void**)&h->d_deliver_cnt, sizeof(uint32_t) * h->max_chunks), "alloc deliver counters");
@@ -730,7 +736,7 @@ int ebag_a2a_reset(ebag_a2a_t h) {
   const DeviceGuard dg(h->device);
   HIP_TRY(dg.error(), "make the plan's device current");
   HIP_TRY(hipDeviceSynchronize(), "synchronize");
-  HIP_TRY(hipMemset(h->d_counters, 0, sizeof(uint32_t) * h->max_flags), "zero counters");
+  HIP_TRY(hipMemset(h->d_counters, 0, sizeof(uint32_t) * (h->max_flags << h->counter_shift)), "zero counters");
   HIP_TRY(hipMemset(h->d_ticket, 0, 2 * sizeof(uint32_t)), "zero run ticket");
   HIP_TRY(hipMemset(h->d_deliver_cnt, 0, sizeof(uint32_t) * h->max_chunks), "zero deliver counters");
   HIP_TRY(hipMemcpy(h->d_status, kStatusInit, sizeof(kStatusInit), hipMemcpyHostToDevice), "reset status");

@@ -389,15 +389,17 @@ __device__ __forceinline__ void store_rows(const float* lds, int nb, int s4, flo
 // writeback.  The arrival that completes the slice re-arms the counter and
 // increments the slice flag.
 __device__ __forceinline__ void release_slice(uint32_t* counters, uint32_t* flags, int64_t g, uint32_t n,
-                                              uint32_t target, int64_t suppress, uint64_t* trace, int mode) {
+                                              uint32_t target, int64_t suppress, uint64_t* trace, int mode,
+                                              int counter_shift) {
+  uint32_t* counter = counters + (g << counter_shift);
   uint32_t old;
   if (mode == 0)
-    old = __hip_atomic_fetch_add(&counters[g], n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    old = __hip_atomic_fetch_add(counter, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   else
-    old = __hip_atomic_fetch_add(&counters[g], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    old = __hip_atomic_fetch_add(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (old + n == target) {
     if (mode == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    __hip_atomic_store(&counters[g], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (trace) trace[g] = wall_clock64();
     if (g != suppress) {
       if (mode == 0)
@@ -557,7 +559,7 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a) {
           if (lane == 0)
             release_slice(a.counters, a.flags, a.per_table ? g * a.T + t : g, (uint32_t)nb,
                           a.per_table ? (uint32_t)a.C : (uint32_t)a.C * (uint32_t)a.T, a.suppress, a.trace_release,
-                          a.release_mode);
+                          a.release_mode, a.counter_shift);
         }
       }
     } else {
@@ -600,7 +602,7 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a) {
       if (threadIdx.x == 0)
         release_slice(a.counters, a.flags, a.per_table ? g * a.T + t : g, (uint32_t)nb,
                       a.per_table ? (uint32_t)a.C : (uint32_t)a.C * (uint32_t)a.T, a.suppress, a.trace_release,
-                      a.release_mode);
+                      a.release_mode, a.counter_shift);
     }
   }
   if (persistent) leave_runs(a.ticket);

@@ -65,6 +65,62 @@ __host__ __device__ inline void run_at(const SliceOrder& o, int32_t T, int32_t J
   *j = (int32_t)(r - *gs * J);
 }
 
+// Division by a launch constant d in [1, 2^31) of numbers below 2^31, as a
+// multiplication (Granlund and Montgomery's round-up method: mul =
+// floor(2^32 (2^shift - d) / d) + 1 with 2^shift >= d).  A division by a
+// variable is a sequence of over twenty vector instructions on this GPU, over a
+// hundred in 64 bits, and would stand at the head of every workgroup's chain
+// of dependent steps; this is three scalar ones.
+struct Divisor {
+  uint32_t d, mul, shift;
+};
+
+// Out-of-range d (of launches that are refused for their run count) is clamped.
+inline Divisor make_divisor(int64_t d) {
+  Divisor v;
+  v.d = d < 1 ? 1u : d > 0x7fffffff ? 0x7fffffffu : (uint32_t)d;
+  v.shift = 0;
+  while (((uint64_t)1 << v.shift) < v.d) ++v.shift;
+  v.mul = (uint32_t)(((((uint64_t)1 << v.shift) - v.d) << 32) / v.d + 1);
+  return v;
+}
+
+__host__ __device__ inline uint32_t divide_by(const Divisor& v, uint32_t n) {
+  return (uint32_t)(((uint64_t)n * v.mul >> 32) + n) >> v.shift;
+}
+
+// run_at for launches of fewer than 2^31 runs, with the order's divisors
+// prepared on the host.
+struct RunOrder {
+  Divisor first;   // slice-major: T * J; table-major: table_groups
+  Divisor second;  // slice-major: T; table-major: n_chunks * J
+  Divisor third;   // table-major: J
+  int32_t table_groups;
+};
+
+inline RunOrder make_run_order(const SliceOrder& o, int32_t T, int32_t J) {
+  RunOrder r;
+  r.table_groups = o.table_groups;
+  r.first = make_divisor(o.table_groups ? o.table_groups : (int64_t)T * J);
+  r.second = make_divisor(o.table_groups ? o.n_chunks * J : T);
+  r.third = make_divisor(J);
+  return r;
+}
+
+__host__ __device__ inline void run_at(const RunOrder& o, uint32_t q, uint32_t* gs, uint32_t* tpos, uint32_t* j) {
+  const uint32_t a = divide_by(o.first, q), x = q - a * o.first.d;
+  if (o.table_groups == 0) {  // a: slice, x: (j, table) inside it
+    *gs = a;
+    *j = divide_by(o.second, x);
+    *tpos = x - *j * o.second.d;
+    return;
+  }
+  const uint32_t k = divide_by(o.second, a), r = a - k * o.second.d;  // x: table group, a: run inside it
+  *tpos = k * o.first.d + x;
+  *gs = divide_by(o.third, r);
+  *j = r - *gs * o.third.d;
+}
+
 struct PoolArgs {
   const void* const* tables;  // [T] table base pointers
   const TabMeta* meta;        // [T]
@@ -82,6 +138,8 @@ struct PoolArgs {
   int64_t nruns;
   int64_t suppress;           // flag index never released (-1: none)
   SliceOrder so;
+  RunOrder ro;
+  Divisor by_waves;           // waves
   int32_t T;
   int32_t C;
   int32_t K;                  // bags per run
@@ -90,7 +148,7 @@ struct PoolArgs {
   int32_t check;              // check offsets / indices
   int32_t release_mode;       // 0 agent-scope release fence, 1 device-scope stores + completion wait
   int32_t waves;              // wavefronts per workgroup (blockDim.x / 64)
-  int32_t out_floats;         // LDS output buffer of the fast path: K x max dim
+  int32_t out_floats;         // LDS output buffer of the fast path: K x max dim (mean: and K lengths)
   int32_t stream_rows;        // 1: table rows loaded non-temporally
   int32_t mean;               // 1: mean pooling (sum / bag length)
   int32_t per_table;          // 1: one flag / counter per (slice, table), index g * T + t
@@ -155,7 +213,7 @@ void clear_error();
 // Launchers (return hipError_t of the launch).
 hipError_t launch_pool(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, const PoolArgs& a,
                        int grid, int block, hipStream_t stream);
-int pool_max_wgs_per_cu(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, int block,
-                        int out_floats);
+int pool_max_wgs_per_cu(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, bool stream_rows,
+                        int block, int out_floats);
 
 }  // namespace ebag

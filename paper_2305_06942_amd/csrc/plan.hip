@@ -310,11 +310,13 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->nruns = so.n_chunks * (int64_t)s.T * a->J;
   a->suppress = o.debug_suppress_flag;
   a->so = so;
+  a->ro = make_run_order(so, s.T, a->J);
+  a->by_waves = make_divisor(o.waves_per_wg);
   a->sum_dim = s.sum_dim;
   a->check = o.check_indices;
   a->release_mode = o.release_mode;
   a->waves = o.waves_per_wg;
-  a->out_floats = K * max_dim;
+  a->out_floats = K * max_dim + (o.pooling_mode == 1 ? (K + 3) & ~3 : 0);
   a->stream_rows = o.stream_rows;
   a->mean = o.pooling_mode == 1;
   a->per_table = o.slice_granule == 1;
@@ -337,7 +339,8 @@ int ebag::pool_grid(const PoolSetup& s, int64_t nruns, bool fused, bool weighted
   if (s.o->persistent_wgs_per_cu != 0) {
     int per_cu = s.o->persistent_wgs_per_cu;
     if (per_cu < 0)
-      per_cu = pool_max_wgs_per_cu(s.dtype, s.o->rows_in_flight, weighted, fused, needs_safe(s), block, out_floats);
+      per_cu = pool_max_wgs_per_cu(s.dtype, s.o->rows_in_flight, weighted, fused, needs_safe(s),
+                                   s.o->stream_rows, block, out_floats);
     if (per_cu < 1) per_cu = 1;
     const int64_t pg = (int64_t)per_cu * s.num_cus;
     if (pg < grid) grid = pg;
@@ -773,8 +776,8 @@ int ebag_a2a_occupancy(ebag_a2a_t h, int32_t weighted, int32_t out[4]) {
   std::memset(&so, 0, sizeof so);
   fill_pool_args(setup_of(h), nullptr, nullptr, nullptr, 0, so, nullptr, nullptr, &a);
   const int block = 64 * h->opts.waves_per_wg;
-  const int n = pool_max_wgs_per_cu(h->dtype, h->opts.rows_in_flight, weighted != 0, true, needs_safe(setup_of(h)), block,
-                                    a.out_floats);
+  const int n = pool_max_wgs_per_cu(h->dtype, h->opts.rows_in_flight, weighted != 0, true, needs_safe(setup_of(h)),
+                                    h->opts.stream_rows, block, a.out_floats);
   if (n <= 0) return fail(EBAG_EHIP, "occupancy query failed");
   out[0] = n;
   out[1] = h->num_cus;

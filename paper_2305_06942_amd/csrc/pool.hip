@@ -13,15 +13,24 @@
 // whole rows (1 KiB) with fully coalesced 16-byte loads; every wave keeps U
 // such loads in flight.  A wave's block of bags has its index run staged in
 // LDS with coalesced loads and read back by broadcast.  Partial sums of the G
-// groups are combined with cross-lane xor-shuffles.
+// groups are combined across lanes.
 //
-// Fast path (tables < 4 GiB, V = 2^k, no index checks): each pooled row goes
-// to an LDS tile of the run; the last wave of the workgroup to finish writes
-// the whole run to its destination slots with contiguous 16-byte stores,
-// waits for them and updates the slice counter -- no workgroup barrier, and
-// no store queued ahead of a gather load.  General path (any width, index
-// checks): per-bag staging, rows stored directly, a barrier before the
-// counter update.
+// Fast path (tables < 4 GiB, V = 2^k, no index checks): the U loads in flight
+// are the next ones of the wave's whole block, of one bag or of several
+// (gather_bags); each pooled row goes to an LDS tile of the run; the last wave
+// of the workgroup to finish writes the whole run to its destination slots
+// with contiguous 16-byte stores, waits for them and updates the slice counter
+// -- no workgroup barrier, and no store queued ahead of a gather load.
+// Long bags are bound by the memory system (512-byte rows arrive at the rate of
+// a random-row read probe); short ones by the waves in flight and by
+// instructions issued per bag, which is why the run's decoding divides by
+// multiplication, the kernel's arguments are re-read instead of kept
+// (late_args) and groups combine without LDS.  Measured at 26 tables x 16384
+// bags of 0 to 3 rows of 512 bytes (547 MB): 188 us with one bag at a time and
+// 81 vector registers (5 waves per SIMD), 112 us with 56 (8 waves), 4.9 TB/s;
+// 24 to 64 rows a bag are level within the 2% that buffer placement moves them.
+// General path (any width, index checks): per-bag staging, rows stored
+// directly, a barrier before the counter update.
 //
 // Run order (run_at): by default runs are numbered slice-major (all runs of
 // slice 0, then slice 1 ...), tables fastest inside a slice, so slices
@@ -35,7 +44,9 @@
 namespace ebag {
 namespace {
 
-constexpr int SEG = 128;       // indices staged in LDS per wave per step
+constexpr int SEG = 128;       // indices staged in LDS per wave per step (general kernels)
+constexpr int SEGW = 512;      // indices a wave stages at once for a block of bags (fast kernels)
+constexpr int SLOTW = SEGW + 64;  // its LDS slot: a row group may read up to 63 entries past the last index
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
@@ -129,13 +140,14 @@ constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 // NT: non-temporal (streaming) loads -- rows that will not be read again do
 // not displace reusable lines (such as the pooled output being written) from
 // L2 and the Infinity Cache.
-template <bool NT>
 struct BufRows {
   __amdgpu_buffer_rsrc_t rs;
   uint32_t col;  // byte offset of this lane's 16-byte vector inside a row
-  uint32_t rb;   // row bytes
-  __device__ __forceinline__ u4v load(int32_t r) const {
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, (uint32_t)r * rb + col, 0, NT ? 2 : 0);
+  int shift;     // log2 of the row bytes
+  // Zeros, and no memory access, where !ok: the offset is past any table.
+  template <bool NT>
+  __device__ __forceinline__ u4v load(int32_t r, bool ok) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? ((uint32_t)r << shift) + col : 0xFFFFFFF0u, 0, NT ? 2 : 0);
   }
 };
 
@@ -346,29 +358,153 @@ __device__ __forceinline__ TabMeta load_meta(const TabMeta* p) {
   return m;
 }
 
-// Combine the G row groups and write the bag's pooled row (dim floats) into
-// the workgroup's LDS output buffer (lanes of group 0, EPV floats each);
-// div > 0: mean pooling over div rows.
+// Combine the G = 64 >> vs row groups of a wave: every lane of group 0 ends
+// with the sum over the groups, added pairwise from the farthest (lane xor 32)
+// to the nearest.  Lane moves inside the vector unit (row swaps and rotations)
+// instead of LDS permutes: after the first two steps all rows of 16 lanes hold
+// the same values, and after a rotation by 8 (4, 2, 1) they repeat with that
+// period, so each rotation fetches the value of lane xor 8 (4, 2, 1).
 template <int EPV>
-__device__ __forceinline__ void reduce_to_lds(float* acc, int vs, int lane, float* lrow, int div) {
-  const int V = 1 << vs;
-  for (int msk = 32; msk >= V; msk >>= 1) {
+__device__ __forceinline__ void reduce_groups(float* acc, int vs) {
+  if (vs > 5) return;
 #pragma unroll
-    for (int e = 0; e < EPV; ++e) acc[e] += __shfl_xor(acc[e], msk);
+  for (int e = 0; e < EPV; ++e) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+    acc[e] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   }
-  divide<EPV>(acc, div);
-  if ((lane >> vs) == 0) {
-    float4* d = reinterpret_cast<float4*>(lrow + (lane & (V - 1)) * EPV);
+  if (vs > 4) return;
 #pragma unroll
-    for (int h = 0; h < EPV / 4; ++h) d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+  for (int e = 0; e < EPV; ++e) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+    acc[e] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+  if (vs > 3) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x128, 0xf, 0xf, true));  // row_ror:8
+  if (vs > 2) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x124, 0xf, 0xf, true));  // row_ror:4
+  if (vs > 1) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x122, 0xf, 0xf, true));  // row_ror:2
+  if (vs > 0) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x121, 0xf, 0xf, true));  // row_ror:1
+}
+
+// Stage indices (and weights, SLOTW words behind them) [base, base + n) into
+// this wave's LDS slot, n <= SEGW, 64 at a time through buffer descriptors: the
+// tail's range check costs no instruction, so a block of a few lookups is one
+// load and one LDS write.
+template <bool WT>
+__device__ __forceinline__ void stage_block(const int32_t* idx, const float* wts, int64_t base, int n, int lane,
+                                            int32_t* slot) {
+  const __amdgpu_buffer_rsrc_t ri =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(idx + base), 0, n * 4, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rw =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(WT ? wts + base : nullptr), 0, WT ? n * 4 : 0, kBufferWord3);
+  for (int i0 = 0; i0 < n; i0 += 256) {
+    uint32_t x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u > 0 && i0 + 64 * u >= n) continue;
+      x[u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (i0 + 64 * u + lane) * 4, 0, 0);
+      if (WT) y[u] = __builtin_amdgcn_raw_buffer_load_b32(rw, (i0 + 64 * u + lane) * 4, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u > 0 && i0 + 64 * u >= n) continue;
+      slot[i0 + 64 * u + lane] = (int32_t)x[u];
+      if (WT) slot[SLOTW + i0 + 64 * u + lane] = (int32_t)y[u];
+    }
+  }
+}
+
+// Gather the bags of one staged block (rows of V = 2^vs <= 64 vectors): lane i
+// < c <= 63 holds bag i as first staged lookup << 16 | lookups (0 in lanes >=
+// c).  Lane (g, v) with g = lane >> vs takes vector v of rows g, g + G, ... of
+// each bag (G = 64 / V); G consecutive rows of one bag are one load
+// instruction.  The wave walks these groups of all its bags in order, U at a
+// time, whatever bags they belong to: all U loads are in flight before the
+// first is added, so bags shorter than U * G rows do not leave the wave with a
+// load or two in flight and a round trip to memory per bag.  The bookkeeping
+// is wave-uniform (scalar registers); a lane past its bag's end loads nothing
+// and adds zeros.  A bag's rows are added in the order of its own lookups, so
+// the result does not depend on how bags share a wave.  After a bag's last
+// group the groups are combined and the row is written to lrow (this lane's
+// vector of it), one row of dim floats per bag; closes = false: the block is a
+// piece of one long bag, which goes on.
+template <class E, int U, bool WT, bool NT>
+__device__ __forceinline__ void gather_bags(const BufRows& rows_ld, int vs, int c, uint32_t bags, const int32_t* slot,
+                                            int lane, bool closes, float* acc, float* lrow, int dim) {
+  constexpr int EPV = E::EPV;
+  const int G = 64 >> vs;
+  const int g = lane >> vs;
+  const int32_t* lg = slot + g;
+  // fp16 rows are widened inside a multiply-add by one; the compiler must not
+  // see that it is one, or it would widen and add in two instructions.
+  float one = 1.f;
+  asm("" : "+v"(one));
+  int bag = 0;
+  uint32_t b = __builtin_amdgcn_readlane(bags, 0);
+  int pos = b >> 16, n = b & 0xffff;  // next staged lookup of the bag, lookups left
+  while (bag < c) {
+    int32_t r[U];
+    float wv[U];
+    int cnt[U];
+    uint32_t ends = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cnt[u] = n;
+      r[u] = lg[pos];
+      wv[u] = WT ? (g < n ? __int_as_float(lg[SLOTW + pos]) : 0.f) : one;
+      pos += G;
+      n -= G;
+      if (n <= 0) {
+        ends |= bag < c ? 1u << u : 0u;
+        ++bag;
+        b = __builtin_amdgcn_readlane(bags, min(bag, 63));  // lane 63 holds no bag
+        pos = b >> 16;
+        n = b & 0xffff;
+      }
+    }
+    u4v raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      raw[u] = u4v{0u, 0u, 0u, 0u};
+      if (cnt[u] > 0) raw[u] = rows_ld.template load<NT>(r[u], g < cnt[u]);  // empty bags and the block's end skip
+    }
+    if (!closes) ends = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      Widen<E>::template add<WT>(acc, raw[u], wv[u]);
+      if (ends >> u & 1u) {
+        reduce_groups<EPV>(acc, vs);
+        if (g == 0) {
+          float4* d = reinterpret_cast<float4*>(lrow);
+#pragma unroll
+          for (int h = 0; h < EPV / 4; ++h)
+            d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+        }
+        lrow += dim;
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+      }
+    }
   }
 }
 
 // Write nb pooled rows of dim floats (dim / 4 = 2^s4 float4s each) from LDS
 // to global rows base + i * stride: 64 lanes x 16 bytes per instruction,
-// each row contiguous.
-__device__ __forceinline__ void store_rows(const float* lds, int nb, int s4, float* base, int64_t stride, int dim,
-                                           int lane, bool sc1) {
+// each row contiguous.  len: mean pooling -- row i is divided by len[i] (an
+// IEEE division, so an exact fp32 sum gives the correctly rounded mean), once
+// per stored value rather than at each bag's end in the gather loop.
+__device__ __forceinline__ void store_rows(const float* lds, const float* len, int nb, int s4, float* base,
+                                           int64_t stride, int dim, int lane, bool sc1) {
   const int n4 = 1 << s4;
   const int64_t span = ((int64_t)(nb - 1) * stride + dim) * 4;
   const __amdgpu_buffer_rsrc_t rs = row_rsrc(base, (int)span);
@@ -376,8 +512,12 @@ __device__ __forceinline__ void store_rows(const float* lds, int nb, int s4, flo
   for (int e = lane; e < (nb << s4); e += 64) {
     const int i = e >> s4;
     const int c4 = e & (n4 - 1);
-    const float4 x = l4[e];
-    store16(rs, (int)((int64_t)i * stride * 4) + c4 * 16, x.x, x.y, x.z, x.w, sc1);
+    float4 x = l4[e];
+    if (len) {
+      const float d = len[i];
+      if (d > 0.f) x = make_float4(x.x / d, x.y / d, x.z / d, x.w / d);
+    }
+    store16(rs, (int)((uint32_t)i * (uint32_t)(stride * 4)) + c4 * 16, x.x, x.y, x.z, x.w, sc1);
   }
 }
 
@@ -414,8 +554,6 @@ __device__ __forceinline__ void release_slice(uint32_t* counters, uint32_t* flag
 // included, has completed (for device-scope stores: at device scope).
 __device__ __forceinline__ void wait_stores_complete() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-constexpr int SEGW = 512;  // indices a wave stages at once for a block of bags
-
 // Persistent grid: workgroups claim runs in production order from an atomic
 // ticket (ticket[0]).  The leading barrier makes sure every wave is done with
 // the previous run (its LDS tile and the broadcast slot) before the slot is
@@ -439,42 +577,155 @@ __device__ __forceinline__ void leave_runs(uint32_t* ticket) {
   }
 }
 
-// One workgroup per run: up to K consecutive samples of one table inside one
-// slice.  The counter it feeds is the slice's (target C * T bags) or, with
-// per-table slices, the (slice, table) pair's (target C bags).  On the fast
-// path wave w pools a contiguous block of the run's bags: it reads the
-// block's CSR offsets with scalar loads, stages the block's whole index
-// segment into its LDS slot when it fits (else bag by bag, SEGW at a time),
-// then gathers and reduces every bag into the run's LDS tile.
-template <class E, int U, bool WT, bool FUSED, bool SAFE>
-__device__ __forceinline__ void pool_body(const PoolArgs& a) {
+// The kernel's arguments, read again from the kernel argument segment wherever
+// this is called.  The compiler otherwise loads all of them at the top and
+// keeps them (over fifty scalar registers, beyond what the kernel has left),
+// spilling scalars into the vector registers that bound the waves per SIMD.
+__device__ __forceinline__ const PoolArgs& late_args() {
+  typedef const __attribute__((address_space(4))) PoolArgs KernArgs;
+  KernArgs* p = (KernArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const PoolArgs*)p;
+}
+
+// Fast path: one workgroup per run of up to K consecutive samples of one table
+// inside one slice.  The counter it feeds is the slice's (target C * T bags)
+// or, with per-table slices, the (slice, table) pair's (target C bags).  Wave
+// w pools a contiguous block of the run's bags: it reads the block's CSR
+// offsets (one lane each), stages the block's whole index segment into its
+// LDS slot when it fits (else bag by bag, SEGW at a time), then gathers every
+// bag into the run's LDS tile.
+template <class E, int U, bool WT, bool NT, bool FUSED>
+__device__ __forceinline__ void pool_fast() {
+  constexpr int EPV = E::EPV;
+  extern __shared__ int32_t s_dyn[];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int W = late_args().waves;
+  // LDS: the run's arrival counter and the ticket's broadcast slot, a staging
+  // slot per wave (and one for the weights), the run's pooled rows (K x max
+  // dim floats), with mean pooling their K bag lengths.
+  int32_t* s_arrive = s_dyn;
+  uint32_t* s_tick = reinterpret_cast<uint32_t*>(s_dyn + 1);
+  int32_t* slot = s_dyn + 4 + wid * SLOTW * (WT ? 2 : 1);
+  float* lds_out = reinterpret_cast<float*>(s_dyn + 4 + W * SLOTW * (WT ? 2 : 1));
+  if (threadIdx.x == 0) *s_arrive = 0;
+  __syncthreads();
+  // One-shot grid: workgroup i pools run i.  Persistent grid (fewer
+  // workgroups than runs): runs are claimed from the ticket.
+  const bool persistent = gridDim.x < late_args().nruns;
+  for (uint32_t q = persistent ? draw_run(late_args().ticket, s_tick) : blockIdx.x; q < late_args().nruns;
+       q = persistent ? draw_run(late_args().ticket, s_tick) : 0x7fffffffu) {
+    uint32_t gs, tpos, j;
+    int t, nb, per;
+    int64_t g, b0;
+    {
+      const PoolArgs& a = late_args();
+      run_at(a.ro, q, &gs, &tpos, &j);
+      t = sload(a.tperm, tpos);
+      g = slice_at(a.so, gs);
+      b0 = g * a.C + (int64_t)j * a.K;
+      nb = min(a.K, a.C - (int)j * a.K);
+      per = (int)divide_by(a.by_waves, (uint32_t)(nb + W - 1));
+    }
+    {
+      const PoolArgs& a = late_args();
+      const TabMeta m = load_meta(a.meta + t);
+      BufRows rows_ld;
+      rows_ld.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(sload(a.tables, t)), 0,
+                                                     (int)(uint32_t)(m.rows * m.row_bytes), kBufferWord3);
+      rows_ld.col = (uint32_t)(lane & ((1 << m.vshift) - 1)) * 16u;
+      rows_ld.shift = m.vshift + 4;
+      const int64_t nnz = sload(a.offsets, (int64_t)a.T * a.B);
+      const int64_t* offs = a.offsets + ((int64_t)t * a.B + b0);  // the run's bags
+      const int end = min((wid + 1) * per, nb);
+      float* lrow = lds_out + (lane & ((1 << m.vshift) - 1)) * EPV;
+      float acc[EPV];
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+      for (int blk = wid * per; blk < end; blk += 63) {
+        const int c = min(63, end - blk);
+        // Offsets are clamped into [0, nnz] and each bag into the block's
+        // segment, so malformed CSR input can never drive a read outside the
+        // index array (results are then meaningless but memory-safe).
+        const int64_t off = offs[blk + min(lane, c)];
+        const int64_t seg_lo = min(max(sload(offs, blk), (int64_t)0), nnz);
+        const int64_t seg_hi = min(max(sload(offs, blk + c), seg_lo), nnz);
+        const bool all = seg_hi - seg_lo <= SEGW;  // the block's lookups fit the staging slot
+        if (all) stage_block<WT>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
+        const int64_t rel = min(max(off, seg_lo), seg_hi) - seg_lo;
+        const int64_t len = max((int64_t)__shfl_down(rel, 1) - rel, (int64_t)0);
+        if (a.mean && lane < c) (lds_out + a.out_floats - ((a.K + 3) & ~3))[blk + lane] = (float)(int)len;
+        uint32_t bags = all && lane < c ? (uint32_t)rel << 16 | (uint32_t)len : 0u;
+        int64_t lo = 0, hi = 0;
+        for (int i = 0; i < c;) {
+          bool closes = true;
+          if (!all) {  // bag by bag, SEGW lookups at a time
+            if (lo == hi) {
+              lo = min(max(sload(offs, blk + i), seg_lo), seg_hi);
+              hi = min(max(sload(offs, blk + i + 1), lo), seg_hi);
+            }
+            const int n = (int)min((int64_t)SEGW, hi - lo);
+            stage_block<WT>(a.indices, a.weights, lo, n, lane, slot);
+            bags = lane == 0 ? n : 0;
+            lo += n;
+            closes = lo == hi;
+          }
+          wave_lds_sync();
+          gather_bags<E, U, WT, NT>(rows_ld, m.vshift, all ? c : 1, bags, slot, lane, closes, acc,
+                                    lrow + (blk + i) * m.dim, m.dim);
+          wave_lds_sync();
+          if (closes) i += all ? c : 1;
+        }
+      }
+    }
+    // The last wave to finish its bags writes the whole run from LDS to
+    // global memory and (fused) completes the run for the slice; the other
+    // waves leave at once.  No workgroup barrier, and no store ever sits in
+    // front of a gather load of the same wave.
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(s_arrive, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    old = __builtin_amdgcn_readfirstlane(old);
+    if (old == W - 1) {
+      const PoolArgs& a = late_args();
+      if (lane == 0) __hip_atomic_store(s_arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const int dim = sload(&a.meta[t].dim, 0), col_off = sload(&a.meta[t].col_off, 0);
+      const int s4 = sload(&a.meta[t].vshift, 0) + (EPV == 8 ? 1 : 0);
+      const int64_t stride = FUSED ? a.sum_dim : dim;
+      float* base = a.out + (FUSED ? col_off : a.B * col_off) + b0 * stride;
+      store_rows(lds_out, a.mean ? lds_out + a.out_floats - ((a.K + 3) & ~3) : nullptr, nb, s4, base, stride, dim, lane,
+                 FUSED && a.release_mode == 1);
+      if (FUSED) {
+        if (a.release_mode == 1) wait_stores_complete();
+        if (lane == 0)
+          release_slice(a.counters, a.flags, a.per_table ? g * a.T + t : g, (uint32_t)nb,
+                        a.per_table ? (uint32_t)a.C : (uint32_t)a.C * (uint32_t)a.T, a.suppress, a.trace_release,
+                        a.release_mode, a.counter_shift);
+      }
+    }
+  }
+  if (persistent) leave_runs(late_args().ticket);
+}
+
+// General path: any row width, 64-bit addresses, index checks; per-bag
+// staging, rows stored directly, a barrier before the counter update.
+template <class E, int U, bool WT, bool FUSED>
+__device__ __forceinline__ void pool_safe(const PoolArgs& a) {
   constexpr int EPV = E::EPV;
   extern __shared__ int32_t s_dyn[];
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = a.waves;
-  const int slot = SAFE ? SEG : SEGW;
-  int32_t* lds_i = s_dyn + wid * slot;
-  float* lds_w = WT ? reinterpret_cast<float*>(s_dyn + W * slot) + wid * slot : nullptr;
-  // Fast path: pooled rows of the current run (K x max dim floats, 16-byte
-  // aligned) and the arrival counter of the run's waves.
-  float* lds_out = reinterpret_cast<float*>(s_dyn + W * slot * (WT ? 2 : 1));
-  int32_t* s_arrive = reinterpret_cast<int32_t*>(lds_out + a.out_floats);
-  if (!SAFE) {
-    if (threadIdx.x == 0) *s_arrive = 0;
-    __syncthreads();
-  }
+  int32_t* lds_i = s_dyn + wid * SEG;
+  float* lds_w = WT ? reinterpret_cast<float*>(s_dyn + W * SEG) + wid * SEG : nullptr;
   const bool sc1 = FUSED && a.release_mode == 1;
-  const int64_t nnz = (!SAFE || a.check) ? sload(a.offsets, (int64_t)a.T * a.B) : 0;
-  // One-shot grid: workgroup i pools run i.  Persistent grid (fewer
-  // workgroups than runs): runs are claimed from the ticket.
+  const int64_t nnz = a.check ? sload(a.offsets, (int64_t)a.T * a.B) : 0;
   const bool persistent = gridDim.x < a.nruns;
-  uint32_t* s_tick = SAFE ? reinterpret_cast<uint32_t*>(lds_out) : reinterpret_cast<uint32_t*>(s_arrive + 1);
+  uint32_t* s_tick = reinterpret_cast<uint32_t*>(s_dyn + W * SEG * (WT ? 2 : 1));
   for (int64_t q = persistent ? draw_run(a.ticket, s_tick) : (int64_t)blockIdx.x; q < a.nruns;
        q = persistent ? draw_run(a.ticket, s_tick) : a.nruns) {
-    int64_t gs;
-    int32_t tpos, j;
-    run_at(a.so, a.T, a.J, q, &gs, &tpos, &j);
+    uint32_t gs, tpos, j;
+    run_at(a.ro, (uint32_t)q, &gs, &tpos, &j);
     const int t = sload(a.tperm, tpos);
     const int64_t g = slice_at(a.so, gs);
     const int64_t b0 = g * a.C + (int64_t)j * a.K;
@@ -488,115 +739,39 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a) {
     const int64_t obase = (int64_t)t * a.B;
     const float* outbase = FUSED ? a.out + m.col_off : a.out + a.B * m.col_off;
     const int64_t ostride = FUSED ? a.sum_dim : m.dim;
-    if (!SAFE) {
-      BufRows<false> rl;
-      rl.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(tab), 0, (int)(uint32_t)(m.rows * m.row_bytes),
-                                                kBufferWord3);
-      rl.col = (uint32_t)(lane & ((1 << m.vshift) - 1)) * 16u;
-      rl.rb = (uint32_t)m.row_bytes;
-      BufRows<true> rn;
-      rn.rs = rl.rs;
-      rn.col = rl.col;
-      rn.rb = rl.rb;
-      const bool nt = a.stream_rows;
-      for (int64_t blk = bb; blk < be; blk += 63) {
-        const int c = (int)min((int64_t)63, be - blk);
-        // Offsets are clamped into [0, nnz] and each bag into the block's
-        // segment, so malformed CSR input can never drive a read outside the
-        // index array (results are then meaningless but memory-safe).
-        const int64_t seg_lo = min(max(sload(a.offsets, obase + blk), (int64_t)0), nnz);
-        const int64_t seg_hi = min(max(sload(a.offsets, obase + blk + c), seg_lo), nnz);
-        const int64_t seg_len = seg_hi - seg_lo;
-        const bool all = seg_len <= SEGW;
-        if (all) {
-          stage<WT>(a.indices, a.weights, seg_lo, (int)seg_len, lane, lds_i, lds_w);
+    for (int64_t b = bb; b < be; ++b) {
+      int64_t lo = a.offsets[obase + b];
+      int64_t hi = a.offsets[obase + b + 1];
+      bool bad = false;
+      if (a.check && !(lo >= 0 && lo <= hi && hi <= nnz)) {
+        bad = true;
+        lo = hi = 0;
+      }
+      const int L = (int)(hi - lo);
+      float* orow = const_cast<float*>(outbase) + b * ostride;
+      if (m.vshift >= 0) {
+        GlobalRows rl;
+        rl.colp = tab + (lane & ((1 << m.vshift) - 1)) * 16;
+        rl.rb = (uint32_t)m.row_bytes;
+        float acc[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+        for (int s0 = 0; s0 < L; s0 += SEG) {
+          const int n = min(SEG, L - s0);
+          stage<WT>(a.indices, a.weights, lo + s0, n, lane, lds_i, lds_w);
+          wave_lds_sync();
+          bad |= a.check ? gather_p2<E, U, WT, true>(rl, m.vshift, m.rows, lds_i, lds_w, n, lane, acc)
+                         : gather_p2<E, U, WT, false>(rl, m.vshift, m.rows, lds_i, lds_w, n, lane, acc);
           wave_lds_sync();
         }
-        int64_t lo = seg_lo;
-        for (int i = 0; i < c; ++i) {
-          lo = min(max(sload(a.offsets, obase + blk + i), lo), seg_hi);
-          const int64_t hi = min(max(sload(a.offsets, obase + blk + i + 1), lo), seg_hi);
-          const int L = (int)(hi - lo);
-          float acc[EPV];
-#pragma unroll
-          for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-          if (all) {
-            const int32_t* li = lds_i + (lo - seg_lo);
-            const float* lw = WT ? lds_w + (lo - seg_lo) : nullptr;
-            if (nt)
-              gather_p2<E, U, WT, false>(rn, m.vshift, m.rows, li, lw, L, lane, acc);
-            else
-              gather_p2<E, U, WT, false>(rl, m.vshift, m.rows, li, lw, L, lane, acc);
-          } else {
-            for (int s0 = 0; s0 < L; s0 += SEGW) {
-              const int n = min(SEGW, L - s0);
-              stage<WT>(a.indices, a.weights, lo + s0, n, lane, lds_i, lds_w);
-              wave_lds_sync();
-              if (nt)
-                gather_p2<E, U, WT, false>(rn, m.vshift, m.rows, lds_i, lds_w, n, lane, acc);
-              else
-                gather_p2<E, U, WT, false>(rl, m.vshift, m.rows, lds_i, lds_w, n, lane, acc);
-              wave_lds_sync();
-            }
-          }
-          reduce_to_lds<EPV>(acc, m.vshift, lane, lds_out + (blk + i - b0) * m.dim, a.mean ? L : 0);
-        }
-        if (all) wave_lds_sync();
+        reduce_store<EPV>(acc, m.vshift, lane, orow, m.dim, sc1, a.mean ? L : 0);
+      } else {
+        bad |= pool_bag_generic<E, U, WT>(tab, m, a.indices, a.weights, lo, L, lds_i, lds_w, lane, a.check, orow,
+                                          sc1, a.mean ? L : 0);
       }
-      // The last wave to finish its bags writes the whole run from LDS to
-      // global memory and (fused) completes the run for the slice; the other
-      // waves leave at once.  No workgroup barrier on the fast path, and no
-      // store ever sits in front of a gather load of the same wave.
-      int old = 0;
-      if (lane == 0) old = __hip_atomic_fetch_add(s_arrive, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-      old = __builtin_amdgcn_readfirstlane(old);
-      if (old == W - 1) {
-        if (lane == 0) __hip_atomic_store(s_arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        const int s4 = m.vshift + (EPV == 8 ? 1 : 0);
-        store_rows(lds_out, (int)nb, s4, const_cast<float*>(outbase) + b0 * ostride, ostride, m.dim, lane, sc1);
-        if (FUSED) {
-          if (a.release_mode == 1) wait_stores_complete();
-          if (lane == 0)
-            release_slice(a.counters, a.flags, a.per_table ? g * a.T + t : g, (uint32_t)nb,
-                          a.per_table ? (uint32_t)a.C : (uint32_t)a.C * (uint32_t)a.T, a.suppress, a.trace_release,
-                          a.release_mode, a.counter_shift);
-        }
-      }
-    } else {
-      for (int64_t b = bb; b < be; ++b) {
-        int64_t lo = a.offsets[obase + b];
-        int64_t hi = a.offsets[obase + b + 1];
-        bool bad = false;
-        if (a.check && !(lo >= 0 && lo <= hi && hi <= nnz)) {
-          bad = true;
-          lo = hi = 0;
-        }
-        const int L = (int)(hi - lo);
-        float* orow = const_cast<float*>(outbase) + b * ostride;
-        if (m.vshift >= 0) {
-          GlobalRows rl;
-          rl.colp = tab + (lane & ((1 << m.vshift) - 1)) * 16;
-          rl.rb = (uint32_t)m.row_bytes;
-          float acc[EPV];
-#pragma unroll
-          for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-          for (int s0 = 0; s0 < L; s0 += SEG) {
-            const int n = min(SEG, L - s0);
-            stage<WT>(a.indices, a.weights, lo + s0, n, lane, lds_i, lds_w);
-            wave_lds_sync();
-            bad |= a.check ? gather_p2<E, U, WT, true>(rl, m.vshift, m.rows, lds_i, lds_w, n, lane, acc)
-                           : gather_p2<E, U, WT, false>(rl, m.vshift, m.rows, lds_i, lds_w, n, lane, acc);
-            wave_lds_sync();
-          }
-          reduce_store<EPV>(acc, m.vshift, lane, orow, m.dim, sc1, a.mean ? L : 0);
-        } else {
-          bad |= pool_bag_generic<E, U, WT>(tab, m, a.indices, a.weights, lo, L, lds_i, lds_w, lane, a.check, orow,
-                                            sc1, a.mean ? L : 0);
-        }
-        if (a.check && __any(bad) && lane == 0) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(obase + b));
-      }
+      if (a.check && __any(bad) && lane == 0) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(obase + b));
     }
-    if (FUSED && SAFE) {
+    if (FUSED) {
       if (a.release_mode == 1) wait_stores_complete();
       __syncthreads();
       if (threadIdx.x == 0)
@@ -608,52 +783,64 @@ __device__ __forceinline__ void pool_body(const PoolArgs& a) {
   if (persistent) leave_runs(a.ticket);
 }
 
+// How a launch reads table rows: through one buffer descriptor per table with
+// non-temporal or cached loads (the fast path), or by the general path.
+enum { ROWS_STREAMED = 0, ROWS_CACHED = 1, ROWS_GENERAL = 2 };
+
 // Fused operator: pooled vectors go straight to the send layout and slices
 // are released as they complete.
-template <class E, int U, bool WT, bool SAFE>
+template <class E, int U, bool WT, int ROWS>
 __global__ __launch_bounds__(1024) void fused_pool_kernel(const PoolArgs a) {
-  pool_body<E, U, WT, true, SAFE>(a);
+  if constexpr (ROWS == ROWS_GENERAL)
+    pool_safe<E, U, WT, true>(a);
+  else
+    pool_fast<E, U, WT, ROWS == ROWS_STREAMED, true>();
 }
 
 // Unfused baseline, first kernel: plain per-table EmbeddingBag output.
-template <class E, int U, bool WT, bool SAFE>
+template <class E, int U, bool WT, int ROWS>
 __global__ __launch_bounds__(1024) void unfused_pool_kernel(const PoolArgs a) {
-  pool_body<E, U, WT, false, SAFE>(a);
+  if constexpr (ROWS == ROWS_GENERAL)
+    pool_safe<E, U, WT, false>(a);
+  else
+    pool_fast<E, U, WT, ROWS == ROWS_STREAMED, false>();
 }
 
 typedef void (*pool_fn)(const PoolArgs);
 
-template <class E, int U, bool WT, bool SAFE>
-pool_fn pick_f(bool fused) {
-  return fused ? &fused_pool_kernel<E, U, WT, SAFE> : &unfused_pool_kernel<E, U, WT, SAFE>;
-}
-
-template <class E, int U>
-pool_fn pick_wf(bool weighted, bool fused, bool safe) {
-  if (weighted) return safe ? pick_f<E, U, true, true>(fused) : pick_f<E, U, true, false>(fused);
-  return safe ? pick_f<E, U, false, true>(fused) : pick_f<E, U, false, false>(fused);
-}
-
-template <class E>
-pool_fn pick_u(int u, bool weighted, bool fused, bool safe) {
-  switch (u) {
-    case 4: return pick_wf<E, 4>(weighted, fused, safe);
-    case 16: return pick_wf<E, 16>(weighted, fused, safe);
-    default: return pick_wf<E, 8>(weighted, fused, safe);
+template <class E, int U, bool WT>
+pool_fn pick_r(int rows, bool fused) {
+  switch (rows) {
+    case ROWS_STREAMED:
+      return fused ? &fused_pool_kernel<E, U, WT, ROWS_STREAMED> : &unfused_pool_kernel<E, U, WT, ROWS_STREAMED>;
+    case ROWS_CACHED:
+      return fused ? &fused_pool_kernel<E, U, WT, ROWS_CACHED> : &unfused_pool_kernel<E, U, WT, ROWS_CACHED>;
+    default:
+      return fused ? &fused_pool_kernel<E, U, WT, ROWS_GENERAL> : &unfused_pool_kernel<E, U, WT, ROWS_GENERAL>;
   }
 }
 
-pool_fn pick(int dtype, int u, bool weighted, bool fused, bool safe) {
+template <class E>
+pool_fn pick_u(int u, bool weighted, int rows, bool fused) {
+  switch (u) {
+    case 4: return weighted ? pick_r<E, 4, true>(rows, fused) : pick_r<E, 4, false>(rows, fused);
+    case 16: return weighted ? pick_r<E, 16, true>(rows, fused) : pick_r<E, 16, false>(rows, fused);
+    default: return weighted ? pick_r<E, 8, true>(rows, fused) : pick_r<E, 8, false>(rows, fused);
+  }
+}
+
+pool_fn pick(int dtype, int u, bool weighted, bool fused, bool safe, bool stream_rows) {
+  const int rows = safe ? ROWS_GENERAL : stream_rows ? ROWS_STREAMED : ROWS_CACHED;
   switch (dtype) {
-    case 1: return pick_u<EF16>(u, weighted, fused, safe);
-    case 2: return pick_u<EBF16>(u, weighted, fused, safe);
-    default: return pick_u<EF32>(u, weighted, fused, safe);
+    case 1: return pick_u<EF16>(u, weighted, rows, fused);
+    case 2: return pick_u<EBF16>(u, weighted, rows, fused);
+    default: return pick_u<EF32>(u, weighted, rows, fused);
   }
 }
 
 size_t lds_bytes(bool safe, bool weighted, int block, int out_floats) {
   // + 16 bytes: the run-arrival counter and the ticket broadcast slot
-  const size_t staging = (size_t)(block / 64) * (safe ? SEG : SEGW) * (weighted ? 8 : 4);
+  const size_t staging = (size_t)(block / 64) * (safe ? SEG : SLOTW) * (weighted ? 8 : 4);
   return safe ? staging + 16 : staging + (size_t)out_floats * 4 + 16;
 }
 
@@ -661,15 +848,15 @@ size_t lds_bytes(bool safe, bool weighted, int block, int out_floats) {
 
 hipError_t launch_pool(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, const PoolArgs& a,
                        int grid, int block, hipStream_t stream) {
-  pool_fn f = pick(dtype, rows_in_flight, weighted, fused, safe);
+  pool_fn f = pick(dtype, rows_in_flight, weighted, fused, safe, a.stream_rows);
   hipLaunchKernelGGL(f, dim3(grid), dim3(block), lds_bytes(safe, weighted, block, a.out_floats), stream, a);
   return hipGetLastError();
 }
 
-int pool_max_wgs_per_cu(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, int block,
-                        int out_floats) {
+int pool_max_wgs_per_cu(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, bool stream_rows,
+                        int block, int out_floats) {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(dtype, rows_in_flight, weighted, fused, safe), block,
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, pick(dtype, rows_in_flight, weighted, fused, safe, stream_rows), block,
                                                    lds_bytes(safe, weighted, block, out_floats)) != hipSuccess)
     return 0;
   return n;

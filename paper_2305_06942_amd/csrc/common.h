@@ -176,6 +176,21 @@ struct PoolSetup {
   uint32_t* d_ticket;
 };
 
+// Which of the pooling kernels a launch takes.  any: the one for any tables and
+// for index reports; else every table is below 4 GiB (32-bit offsets) with rows
+// of 2^k <= 64 sixteen-byte vectors, whose kernel needs far fewer registers
+// (fp16: 65 instead of 85) and reads such tables faster (26 tables x 16384 bags
+// of 0 to 3 rows of 512 bytes: 113 us, against 158 us by the other one).
+struct PoolVariant {
+  int dtype;
+  int rows_in_flight;
+  bool weighted, fused, stream_rows, any;
+};
+typedef void (*pool_fn)(const PoolArgs);
+pool_fn pick_pool_f32(const PoolVariant& k);
+pool_fn pick_pool_f16(const PoolVariant& k);
+pool_fn pick_pool_bf16(const PoolVariant& k);
+
 // Host helpers shared by the plan and the plan-free forward (plan.hip).
 constexpr int kMaxXcd = 64;
 
@@ -197,10 +212,10 @@ int check_opts(const ebag_a2a_opts_t& o);
 int xcd_count(int num_cus);
 int32_t table_groups_for(const ebag_a2a_opts_t& o, int32_t T, int n_xcd);
 void table_order(const int64_t* row_bytes, int32_t T, int n_xcd, int32_t* perm, int32_t* work, int64_t* load);
-bool needs_safe(const PoolSetup& s);
+PoolVariant pool_variant(const PoolSetup& s, bool fused, bool weighted);
 void fill_pool_args(const PoolSetup& s, const int32_t* indices, const int64_t* offsets, const float* weights,
                     int64_t B, const SliceOrder& so, float* out, uint32_t* flags, PoolArgs* a);
-int pool_grid(const PoolSetup& s, int64_t nruns, bool fused, bool weighted, int block, int out_floats);
+int pool_grid(const PoolSetup& s, int64_t nruns, const PoolVariant& k, int block, int out_floats);
 
 // Status word layout (int32[4]) and its initial value.
 enum { ST_TIMED_OUT = 0, ST_FIRST_MISSING = 1, ST_OVERSHOOT = 2, ST_FIRST_BAD_BAG = 3 };
@@ -210,10 +225,9 @@ constexpr int32_t kStatusInit[4] = {0, 0x7fffffff, 0, 0x7fffffff};
 int fail(int code, const char* fmt, ...);
 void clear_error();
 
-// Launchers (return hipError_t of the launch).
-hipError_t launch_pool(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, const PoolArgs& a,
-                       int grid, int block, hipStream_t stream);
-int pool_max_wgs_per_cu(int dtype, int rows_in_flight, bool weighted, bool fused, bool safe, bool stream_rows,
-                        int block, int out_floats);
+constexpr int kPoolSlotWords = 576;  // LDS words of a pooling wave's index staging slot
+
+hipError_t launch_pool(const PoolVariant& k, const PoolArgs& a, int grid, int block, hipStream_t stream);
+int pool_max_wgs_per_cu(const PoolVariant& k, int block, int out_floats);
 
 }  // namespace ebag

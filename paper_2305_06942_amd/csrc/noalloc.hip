@@ -211,7 +211,8 @@ extern "C" int ebag_a2a_forward_noalloc(int32_t num_tables, const int64_t* rows_
   fill_pool_args(ps, indices, offsets, weights, B, so, send_buf, flags, &a);
   if (a.nruns >= INT_MAX) return fail(EBAG_EINVAL, "too many runs (%lld) for one launch", (long long)a.nruns);
   const int block = 64 * o.waves_per_wg;
-  const int grid = pool_grid(ps, a.nruns, true, weights != nullptr, block, a.out_floats);
+  const PoolVariant k = pool_variant(ps, true, weights != nullptr);
+  const int grid = pool_grid(ps, a.nruns, k, block, a.out_floats);
 
   // Descriptors in batches of kInstallTables; the first launch also clears
   // the counters, ticket and status word (the previous call on this device
@@ -237,8 +238,7 @@ extern "C" int ebag_a2a_forward_noalloc(int32_t num_tables, const int64_t* rows_
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(EBAG_EHIP, "launch install kernel: %s", hipGetErrorString(e));
   }
-  const hipError_t e = launch_pool(ps.dtype, o.rows_in_flight, weights != nullptr, true, needs_safe(ps), a, grid,
-                                   block, stream);
+  const hipError_t e = launch_pool(k, a, grid, block, stream);
   if (e != hipSuccess) return fail(EBAG_EHIP, "launch fused pooling kernel: %s", hipGetErrorString(e));
   return EBAG_OK;
 }

@@ -316,31 +316,36 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->check = o.check_indices;
   a->release_mode = o.release_mode;
   a->waves = o.waves_per_wg;
-  a->out_floats = K * max_dim + (o.pooling_mode == 1 ? (K + 3) & ~3 : 0);
+  // Rows of more than 64 vectors do not go through the tile.
+  int32_t tile_dim = 0;
+  for (int32_t t = 0; t < s.T; ++t)
+    if (s.meta[t].vecs <= 64 && s.meta[t].dim > tile_dim) tile_dim = s.meta[t].dim;
+  a->out_floats = K * tile_dim + (o.pooling_mode == 1 ? (K + 3) & ~3 : 0);
   a->stream_rows = o.stream_rows;
   a->mean = o.pooling_mode == 1;
   a->per_table = o.slice_granule == 1;
 }
 
-// The fast pooling kernels handle tables below 4 GiB (32-bit buffer offsets)
-// whose rows are 2^k <= 64 sixteen-byte vectors, without index reporting;
-// anything else uses the general kernels.
-bool ebag::needs_safe(const PoolSetup& s) {
-  if (s.o->check_indices) return true;
+PoolVariant ebag::pool_variant(const PoolSetup& s, bool fused, bool weighted) {
+  PoolVariant k;
+  k.dtype = s.dtype;
+  k.rows_in_flight = s.o->rows_in_flight;
+  k.weighted = weighted;
+  k.fused = fused;
+  k.stream_rows = s.o->stream_rows != 0;
+  k.any = s.o->check_indices != 0;
   for (int32_t t = 0; t < s.T; ++t) {
     const TabMeta& m = s.meta[t];
-    if (m.vshift < 0 || m.rows * m.row_bytes > (int64_t)0xFFFFFFFFll) return true;
+    if (m.vshift < 0 || m.rows * m.row_bytes > (int64_t)0xFFFFFFFFll) k.any = true;
   }
-  return false;
+  return k;
 }
 
-int ebag::pool_grid(const PoolSetup& s, int64_t nruns, bool fused, bool weighted, int block, int out_floats) {
+int ebag::pool_grid(const PoolSetup& s, int64_t nruns, const PoolVariant& k, int block, int out_floats) {
   int64_t grid = nruns;
   if (s.o->persistent_wgs_per_cu != 0) {
     int per_cu = s.o->persistent_wgs_per_cu;
-    if (per_cu < 0)
-      per_cu = pool_max_wgs_per_cu(s.dtype, s.o->rows_in_flight, weighted, fused, needs_safe(s),
-                                   s.o->stream_rows, block, out_floats);
+    if (per_cu < 0) per_cu = pool_max_wgs_per_cu(k, block, out_floats);
     if (per_cu < 1) per_cu = 1;
     const int64_t pg = (int64_t)per_cu * s.num_cus;
     if (pg < grid) grid = pg;
@@ -527,9 +532,8 @@ int ebag_a2a_forward(ebag_a2a_t h, const void* const* tables, const int32_t* ind
   if (a.nruns >= INT_MAX) return fail(EBAG_EINVAL, "too many runs (%lld) for one launch", (long long)a.nruns);
   rc = sync_tables(h, tables, stream);
   if (rc) return rc;
-  const int grid = pool_grid(setup_of(h), a.nruns, true, weights != nullptr, block, a.out_floats);
-  hipError_t e = launch_pool(h->dtype, h->opts.rows_in_flight, weights != nullptr, true, needs_safe(setup_of(h)), a, grid,
-                             block, stream);
+  const PoolVariant k = pool_variant(setup_of(h), true, weights != nullptr);
+  hipError_t e = launch_pool(k, a, pool_grid(setup_of(h), a.nruns, k, block, a.out_floats), block, stream);
   if (e != hipSuccess) return hip_fail(e, "launch fused pooling kernel");
   return note_call(h->fwd, stream);
 }
@@ -549,9 +553,8 @@ int ebag_a2a_unfused_forward(ebag_a2a_t h, const void* const* tables, const int3
   if (so.n_chunks * h->T > INT_MAX) return fail(EBAG_EINVAL, "too many slices x tables for the repack grid");
   rc = sync_tables(h, tables, stream);
   if (rc) return rc;
-  const int grid = pool_grid(setup_of(h), a.nruns, false, weights != nullptr, block, a.out_floats);
-  hipError_t e = launch_pool(h->dtype, h->opts.rows_in_flight, weights != nullptr, false, needs_safe(setup_of(h)), a, grid,
-                             block, stream);
+  const PoolVariant k = pool_variant(setup_of(h), false, weights != nullptr);
+  hipError_t e = launch_pool(k, a, pool_grid(setup_of(h), a.nruns, k, block, a.out_floats), block, stream);
   if (e != hipSuccess) return hip_fail(e, "launch pooling kernel");
   RepackArgs r;
   std::memset(&r, 0, sizeof r);
@@ -776,8 +779,7 @@ int ebag_a2a_occupancy(ebag_a2a_t h, int32_t weighted, int32_t out[4]) {
   std::memset(&so, 0, sizeof so);
   fill_pool_args(setup_of(h), nullptr, nullptr, nullptr, 0, so, nullptr, nullptr, &a);
   const int block = 64 * h->opts.waves_per_wg;
-  const int n = pool_max_wgs_per_cu(h->dtype, h->opts.rows_in_flight, weighted != 0, true, needs_safe(setup_of(h)),
-                                    h->opts.stream_rows, block, a.out_floats);
+  const int n = pool_max_wgs_per_cu(pool_variant(setup_of(h), true, weighted != 0), block, a.out_floats);
   if (n <= 0) return fail(EBAG_EHIP, "occupancy query failed");
   out[0] = n;
   out[1] = h->num_cus;

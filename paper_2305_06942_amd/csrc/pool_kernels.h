@@ -1,0 +1,735 @@
+// Embedding-bag pooling kernels for gfx950.  Templates over the storage type;
+// each type's kernels are instantiated in a source file of their own
+// (pool_f32.hip, pool_f16.hip, pool_bf16.hip), which compile side by side.
+//
+// One wavefront pools one bag at a time (the paper's "logical workgroup" of
+// the EmbeddingBag kernel, Sec. III-A).  A workgroup takes a *run* of up to K
+// consecutive samples of one table inside one slice and its waves share the
+// run's bags; after the run the workgroup bumps that slice's counter once,
+// and the arrival that completes the slice releases the slice's flag
+// (Sec. III-A, "Book-keeping Flags").
+//
+// Gather: a row of D_t elements is V = D_t*elt/16 sixteen-byte vectors.  For
+// V a power of two <= 64 the 64 lanes form G = 64/V row groups, lane (g, v)
+// loads vector v of rows g, g+G, g+2G, ... so one wave instruction fetches G
+// whole rows (1 KiB) with fully coalesced 16-byte loads; every wave keeps U
+// such loads in flight.  A wave's block of bags has its index run staged in
+// LDS with coalesced loads and read back by broadcast.  Partial sums of the G
+// groups are combined across lanes.
+//
+// The U loads in flight are the next ones of the wave's whole block, of one bag
+// or of several (gather_bags); each pooled row goes to an LDS tile of the run;
+// the last wave of the workgroup to finish writes the whole run to its
+// destination slots with contiguous 16-byte stores, waits for them and updates
+// the slice counter -- no workgroup barrier, and no store queued ahead of a
+// gather load.  Tables below 4 GiB with V = 2^k and no index report take the
+// fast kernel (FastTable); any others the general one (AnyTable): G = 64/V
+// rounded down, V > 64 pooled 64 vectors at a time and stored directly.
+// Long bags are bound by the memory system (512-byte rows arrive at the rate of
+// a random-row read probe); short ones by the waves in flight and by
+// instructions issued per bag, which is why the run's decoding divides by
+// multiplication, the kernel's arguments are re-read instead of kept
+// (late_args) and groups combine without LDS.  Measured at 26 tables x 16384
+// bags of 0 to 3 rows of 512 bytes (547 MB): 188 us with one bag at a time and
+// 81 vector registers (5 waves per SIMD), 112 us with 56 (8 waves), 4.9 TB/s;
+// 24 to 64 rows a bag are level (within 0.5% on the same buffers).
+//
+// Run order (run_at): by default runs are numbered slice-major (all runs of
+// slice 0, then slice 1 ...), tables fastest inside a slice, so slices
+// complete progressively and a consumer can drain them while later slices
+// are still being pooled.  Table-major order pools one table at a time, on
+// each XCD separately (table_major = 1: the table's hot rows stay in that
+// XCD's L2) or on the whole device (table_major = 2: the table shares the
+// Infinity Cache); with per-table slices those still complete progressively.
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+
+namespace ebag {
+namespace {
+
+constexpr int SEGW = 512;         // indices a wave stages at once for a block of bags
+// A wave's LDS slot: a row group may read up to 63 entries past the last index.
+static_assert(kPoolSlotWords >= SEGW + 64, "staging slot");
+
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+struct EF32 { static constexpr int EPV = 4; };
+struct EF16 { static constexpr int EPV = 8; };
+struct EBF16 { static constexpr int EPV = 8; };
+
+template <class E> struct Widen;
+
+template <> struct Widen<EF32> {
+  template <bool WT>
+  static __device__ __forceinline__ void add(float* acc, const u4v& r, float w) {
+    const float x[4] = {__uint_as_float(r.x), __uint_as_float(r.y), __uint_as_float(r.z), __uint_as_float(r.w)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = WT ? __builtin_fmaf(w, x[e], acc[e]) : acc[e] + x[e];
+  }
+};
+
+__device__ __forceinline__ float h2f(uint32_t bits16) {
+  return (float)__builtin_bit_cast(_Float16, (uint16_t)bits16);
+}
+
+// fp16 rows: every element goes through one fma(w, widen(h), acc), also
+// without weights.  There the caller's w is 1 for a row it loaded and 0 for a
+// slot it left empty (whose row bits are zero), a value the compiler cannot
+// fold, so it emits one mixed-precision FMA per element (the fp16 operand is
+// widened inside the instruction) instead of a convert and an add.  Since
+// 1 * x and 0 * (+0) are exact, the single rounding gives the bits acc + x and
+// acc + 0 would: the result does not change, only the instruction count.
+template <> struct Widen<EF16> {
+  template <bool WT>
+  static __device__ __forceinline__ void add(float* acc, const u4v& r, float w) {
+    const uint32_t u[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = h2f(u[e] & 0xffffu), hi = h2f(u[e] >> 16);
+      acc[2 * e] = __builtin_fmaf(w, lo, acc[2 * e]);
+      acc[2 * e + 1] = __builtin_fmaf(w, hi, acc[2 * e + 1]);
+    }
+  }
+};
+
+template <> struct Widen<EBF16> {
+  template <bool WT>
+  static __device__ __forceinline__ void add(float* acc, const u4v& r, float w) {
+    const uint32_t u[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __uint_as_float(u[e] << 16), hi = __uint_as_float(u[e] & 0xffff0000u);
+      acc[2 * e] = WT ? __builtin_fmaf(w, lo, acc[2 * e]) : acc[2 * e] + lo;
+      acc[2 * e + 1] = WT ? __builtin_fmaf(w, hi, acc[2 * e + 1]) : acc[2 * e + 1] + hi;
+    }
+  }
+};
+
+// LDS written by some lanes of a wave and read by others: keep the compiler
+// from reordering across this point and wait for the LDS writes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Table rows live in global memory; say so, so the loads are global_load
+// (vmcnt only) rather than flat loads that would also hold up LDS reads.
+typedef __attribute__((address_space(1))) const u4v gu4v;
+constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
+
+// Output stores go through a buffer descriptor spanning exactly one pooled
+// row (out-of-range lanes are dropped by the hardware).  sc1 = 1 gives
+// device-scope stores: they complete at device scope, so a release needs no
+// L2 writeback for them; sc1 = 0 gives plain write-back stores.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(float* row, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(row, 0, bytes, kBufferWord3);
+}
+
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, int off, float a, float b, float c, float d,
+                                        bool sc1) {
+  const u4v x = {__float_as_uint(a), __float_as_uint(b), __float_as_uint(c), __float_as_uint(d)};
+  if (sc1)
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, 16);
+  else
+    __builtin_amdgcn_raw_buffer_store_b128(x, r, off, 0, 0);
+}
+
+// Read-only inputs read with wave-uniform addresses (table order, table
+// constants and pointers, CSR offsets) go through the scalar data cache:
+// their latency then does not queue behind the row gathers in the vector
+// memory pipeline.  Nothing the kernel writes is read this way.
+template <class T>
+__device__ __forceinline__ T sload(const T* p, int64_t i) {
+  return ((const __attribute__((address_space(4))) T*)p)[i];
+}
+
+__device__ __forceinline__ TabMeta load_meta(const TabMeta* p) {
+  TabMeta m;
+  m.rows = sload(&p->rows, 0);
+  m.row_bytes = sload(&p->row_bytes, 0);
+  m.dim = sload(&p->dim, 0);
+  m.col_off = sload(&p->col_off, 0);
+  m.vecs = sload(&p->vecs, 0);
+  m.vshift = sload(&p->vshift, 0);
+  return m;
+}
+
+// Combine the G = 64 >> vs row groups of a wave: every lane of group 0 ends
+// with the sum over the groups, added pairwise from the farthest (lane xor 32)
+// to the nearest.  Lane moves inside the vector unit (row swaps and rotations)
+// instead of LDS permutes: after the first two steps all rows of 16 lanes hold
+// the same values, and after a rotation by 8 (4, 2, 1) they repeat with that
+// period, so each rotation fetches the value of lane xor 8 (4, 2, 1).
+template <int EPV>
+__device__ __forceinline__ void reduce_groups(float* acc, int vs) {
+  if (vs > 5) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+    acc[e] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+  if (vs > 4) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[e]), __float_as_uint(acc[e]), false, false);
+    acc[e] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+  if (vs > 3) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x128, 0xf, 0xf, true));  // row_ror:8
+  if (vs > 2) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x124, 0xf, 0xf, true));  // row_ror:4
+  if (vs > 1) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x122, 0xf, 0xf, true));  // row_ror:2
+  if (vs > 0) return;
+#pragma unroll
+  for (int e = 0; e < EPV; ++e)
+    acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x121, 0xf, 0xf, true));  // row_ror:1
+}
+
+// Stage indices (and weights, kPoolSlotWords words behind them) [base, base + n) into
+// this wave's LDS slot, n <= SEGW, 64 at a time through buffer descriptors: the
+// tail's range check costs no instruction, so a block of a few lookups is one
+// load and one LDS write.
+template <bool WT>
+__device__ __forceinline__ void stage_block(const int32_t* idx, const float* wts, int64_t base, int n, int lane,
+                                            int32_t* slot) {
+  const __amdgpu_buffer_rsrc_t ri =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(idx + base), 0, n * 4, kBufferWord3);
+  const __amdgpu_buffer_rsrc_t rw =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(WT ? wts + base : nullptr), 0, WT ? n * 4 : 0, kBufferWord3);
+  for (int i0 = 0; i0 < n; i0 += 256) {
+    uint32_t x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u > 0 && i0 + 64 * u >= n) continue;
+      x[u] = __builtin_amdgcn_raw_buffer_load_b32(ri, (i0 + 64 * u + lane) * 4, 0, 0);
+      if (WT) y[u] = __builtin_amdgcn_raw_buffer_load_b32(rw, (i0 + 64 * u + lane) * 4, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (u > 0 && i0 + 64 * u >= n) continue;
+      slot[i0 + 64 * u + lane] = (int32_t)x[u];
+      if (WT) slot[kPoolSlotWords + i0 + 64 * u + lane] = (int32_t)y[u];
+    }
+  }
+}
+
+// The kernel's arguments, read again from the kernel argument segment wherever
+// this is called.  The compiler otherwise loads all of them at the top and
+// keeps them (over fifty scalar registers, beyond what the kernel has left),
+// spilling scalars into the vector registers that bound the waves per SIMD.
+__device__ __forceinline__ const PoolArgs& late_args() {
+  typedef const __attribute__((address_space(4))) PoolArgs KernArgs;
+  KernArgs* p = (KernArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const PoolArgs*)p;
+}
+
+// A column block of Vb <= 64 sixteen-byte vectors of one table's rows, as the
+// lanes of a wave read it: lane (g, v) takes vector v of a row of group g, G =
+// 64 / Vb groups (rounded down; the lanes left over read nothing).  A pooled
+// row leaves through emit(): to the run's LDS tile (lrow: this lane's vector of
+// the next bag's row), or where a row has more than 64 vectors and takes
+// several blocks, straight to its destination.
+//
+// Fast tables (below 4 GiB, rows of 2^k <= 64 vectors, no index report): loads
+// go through a buffer descriptor covering exactly the table.  32-bit offsets
+// keep one address register per load instead of two, and the hardware range
+// check turns any offset past the table into zeros, so even invalid indices
+// cannot read outside it.  NT: non-temporal (streaming) loads -- rows that will
+// not be read again do not displace reusable lines (such as the pooled output
+// being written) from L2 and the Infinity Cache.
+template <int EPV, bool NT>
+struct FastTable {
+  static constexpr bool CHECKS = false;
+  __amdgpu_buffer_rsrc_t rs;
+  uint32_t col;  // byte offset of this lane's 16-byte vector inside a row
+  int vs;        // log2 of the vectors per row
+  int g;
+  float* lrow;
+  int dim;
+  __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int lane) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(tab), 0, (int)(uint32_t)(m.rows * m.row_bytes),
+                                           kBufferWord3);
+    vs = m.vshift;
+    g = lane >> vs;
+    col = (uint32_t)(lane & ((1 << vs) - 1)) * 16u;
+    dim = m.dim;
+  }
+  __device__ __forceinline__ int groups() const { return 64 >> vs; }
+  __device__ __forceinline__ int slot_lane() const { return g; }
+  // Zeros, and no memory access, in lanes past the bag's end: their offset is
+  // past any table.
+  __device__ __forceinline__ u4v load(int32_t r, int left, bool*) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, g < left ? ((uint32_t)r << (vs + 4)) + col : 0xFFFFFFF0u, 0,
+                                                 NT ? 2 : 0);
+  }
+  __device__ __forceinline__ void emit(float* acc) {
+    reduce_groups<EPV>(acc, vs);
+    if (g == 0) {
+      float4* d = reinterpret_cast<float4*>(lrow);
+#pragma unroll
+      for (int h = 0; h < EPV / 4; ++h)
+        d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+    }
+    lrow += dim;
+  }
+};
+
+// Any table: any row width, 64-bit addresses, indices checked against the table
+// (a row out of range is skipped, and reported by the caller when the plan asks
+// for it).  Measured on 24 fp16 tables of 96 to 640-byte rows, bags of 1 to 40
+// (0.94 GB): 292 us with one row a load and one bag at a time, 236 us like this
+// -- its rows touch 8.7 M cache lines, which random reads return in about 175
+// us; reading tables below 4 GiB through a buffer descriptor here too left it
+// at 236 us.  Four fp32 tables of 5.1 GB, mean of 1 to 40 rows of 512 bytes
+// (0.72 GB): 156 us before, 141 us.
+template <int EPV, bool NT, bool FUSED>
+struct AnyTable {
+  static constexpr bool CHECKS = true;
+  const char* colp;   // this lane's vector of row 0
+  uint32_t rows, rb;
+  int vb, G, g, v;    // g: beyond any bag in the lanes left over
+  bool tile;          // rows of at most 64 vectors leave through the LDS tile
+  float* lrow;
+  int dim;
+  int first;          // direct: first vector of the block,
+  int t;              // the table,
+  int64_t bag;        // the next bag's sample
+  const float* len;   // and, mean pooling, its length
+  __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int block, int lane) {
+    rows = (uint32_t)m.rows;
+    rb = (uint32_t)m.row_bytes;
+    dim = m.dim;
+    first = block;
+    vb = min(64, m.vecs - block);
+    G = (int)(64u / (unsigned)vb);
+    g = (int)((unsigned)lane / (unsigned)vb);
+    v = lane - g * vb;
+    if (g >= G) g = 1 << 20;
+    colp = static_cast<const char*>(tab) + (int64_t)(block + v) * 16;
+  }
+  __device__ __forceinline__ int groups() const { return G; }
+  __device__ __forceinline__ int slot_lane() const { return g < G ? g : 0; }
+  __device__ __forceinline__ u4v load(int32_t r, int left, bool* bad) const {
+    const bool in = (uint32_t)r < rows;
+    *bad = g < left && !in;
+    u4v x = {0u, 0u, 0u, 0u};
+    if (g < left && in) {
+      gu4v* p = (gu4v*)(colp + (uint64_t)(uint32_t)r * rb);
+      x = NT ? __builtin_nontemporal_load(p) : *p;
+    }
+    return x;
+  }
+  __device__ __forceinline__ void emit(float* acc) {
+    for (int s = 32; s > 0; s >>= 1) {  // group g < s takes in group g + s, farthest first
+      if (s >= G) continue;
+      const bool take = g < s && g + s < G;
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) {
+        const float x = __shfl(acc[e], (int)(threadIdx.x & 63) + s * vb);
+        acc[e] = take ? acc[e] + x : acc[e];
+      }
+    }
+    if (tile) {
+      if (g == 0) {
+        float4* d = reinterpret_cast<float4*>(lrow);
+#pragma unroll
+        for (int h = 0; h < EPV / 4; ++h)
+          d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+      }
+      lrow += dim;
+      return;
+    }
+    store_row(acc);
+    ++bag;
+    ++len;
+  }
+  __device__ __forceinline__ void store_row(float* acc) const {
+    const PoolArgs& a = late_args();
+    if (a.mean) {
+      const float d = *len;
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) acc[e] = d > 0.f ? acc[e] / d : acc[e];
+    }
+    const int col_off = sload(&a.meta[t].col_off, 0);
+    float* row = a.out + (FUSED ? bag * a.sum_dim + col_off : a.B * col_off + bag * dim);
+    if (g == 0) {
+      const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, dim * 4);
+#pragma unroll
+      for (int h = 0; h < EPV / 4; ++h)
+        store16(rs, ((first + v) * EPV + 4 * h) * 4, acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3],
+                FUSED && a.release_mode == 1);
+    }
+  }
+};
+
+// Gather the bags of one staged block: lane i < c <= 63 holds bag i as first
+// staged lookup << 16 | lookups (0 in lanes >= c).  Lane (g, v) takes vector v
+// of rows g, g + G, ... of each bag; G consecutive rows of one bag are one load
+// instruction.  The wave walks these groups of all its bags in order, U at a
+// time, whatever bags they belong to: all U loads are in flight before the
+// first is added, so bags shorter than U * G rows do not leave the wave with a
+// load or two in flight and a round trip to memory per bag.  The bookkeeping
+// is wave-uniform (scalar registers); a lane past its bag's end loads nothing
+// and adds zeros.  A bag's rows are added in the order of its own lookups, so
+// the result does not depend on how bags share a wave.  After a bag's last
+// group its row is emitted; closes = false: the block is a piece of one long
+// bag, which goes on.  A bag with an index out of range reports itself: bad
+// carries over the pieces of one bag, report is the first bag's number (or
+// nullptr status).
+template <class E, int U, bool WT, class Table>
+__device__ __forceinline__ void gather_bags(Table& tb, int c, uint32_t bags, const int32_t* slot, int lane,
+                                            bool closes, float* acc, int32_t* status, int64_t report, bool* carry) {
+  constexpr int EPV = E::EPV;
+  const int G = tb.groups();
+  const int g = tb.g;
+  const int32_t* lg = slot + tb.slot_lane();
+  // fp16 rows are widened inside a multiply-add by one; the compiler must not
+  // see that it is one, or it would widen and add in two instructions.
+  float one = 1.f;
+  asm("" : "+v"(one));
+  int bag = 0;
+  uint32_t b = __builtin_amdgcn_readlane(bags, 0);
+  int pos = b >> 16, n = b & 0xffff;  // next staged lookup of the bag, lookups left
+  while (bag < c) {
+    int32_t r[U];
+    float wv[U];
+    int cnt[U];
+    uint32_t ends = 0, bads = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cnt[u] = n;
+      r[u] = lg[pos];
+      wv[u] = WT ? (g < n ? __int_as_float(lg[kPoolSlotWords + pos]) : 0.f) : one;
+      pos += G;
+      n -= G;
+      if (n <= 0) {
+        ends |= bag < c ? 1u << u : 0u;
+        ++bag;
+        b = __builtin_amdgcn_readlane(bags, min(bag, 63));  // lane 63 holds no bag
+        pos = b >> 16;
+        n = b & 0xffff;
+      }
+    }
+    u4v raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      raw[u] = u4v{0u, 0u, 0u, 0u};
+      if (cnt[u] > 0) {  // empty bags and the block's end skip
+        bool bad = false;
+        raw[u] = tb.load(r[u], cnt[u], &bad);
+        if (Table::CHECKS && status) bads |= __any(bad) ? 1u << u : 0u;
+      }
+    }
+    if (!closes) ends = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      Widen<E>::template add<WT>(acc, raw[u], wv[u]);
+      if (Table::CHECKS) *carry |= bads >> u & 1u;
+      if (ends >> u & 1u) {
+        tb.emit(acc);
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+        if (Table::CHECKS) {
+          if (*carry && lane == 0) atomicMin(&status[ST_FIRST_BAD_BAG], (int32_t)report);
+          *carry = false;
+          ++report;
+        }
+      }
+    }
+  }
+}
+
+// Write nb pooled rows of dim floats from LDS to global rows base + i * stride:
+// 64 lanes x 16 bytes per instruction, each row contiguous; a lane steps its
+// (row, vector) by 64 vectors; P2: dim is a power of two.  len:
+// mean pooling -- row i is divided by len[i] (an IEEE division, so an exact
+// fp32 sum gives the correctly rounded mean), once per stored value rather
+// than at each bag's end in the gather loop.
+template <bool P2>
+__device__ __forceinline__ void store_rows(const float* lds, const float* len, int nb, float* base, int64_t stride,
+                                           int dim, int lane, bool sc1) {
+  const unsigned n4 = (unsigned)dim >> 2;
+  const int64_t span = ((int64_t)(nb - 1) * stride + dim) * 4;
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(base, (int)span);
+  const float4* l4 = reinterpret_cast<const float4*>(lds);
+  const int total = nb * (int)n4;
+  const int s4 = P2 ? __builtin_ctz(n4) : 0;
+  const int dr = (int)(P2 ? 64u >> s4 : 64u / n4), dc = (int)(64u - dr * n4);
+  int i = (int)(P2 ? (unsigned)lane >> s4 : (unsigned)lane / n4), c4 = lane - i * (int)n4;
+  for (int e = lane; e < total; e += 64) {
+    float4 x = l4[e];
+    if (len) {
+      const float d = len[i];
+      if (d > 0.f) x = make_float4(x.x / d, x.y / d, x.z / d, x.w / d);
+    }
+    store16(rs, (int)((uint32_t)i * (uint32_t)(stride * 4)) + c4 * 16, x.x, x.y, x.z, x.w, sc1);
+    i += dr;
+    c4 += dc;
+    if (c4 >= (int)n4) {
+      c4 -= (int)n4;
+      ++i;
+    }
+  }
+}
+
+// Completion of one run (fused only).  release_mode 0: the workgroup's
+// stores are published by an agent-scope release on the slice counter (an L2
+// writeback on every run).  release_mode 1: the pooled vectors were stored
+// with device-scope stores, each wave waited for them to complete at device
+// scope (vmcnt 0) before the barrier, so the counter update needs no cache
+// writeback.  The arrival that completes the slice re-arms the counter and
+// increments the slice flag.
+__device__ __forceinline__ void release_slice(uint32_t* counters, uint32_t* flags, int64_t g, uint32_t n,
+                                              uint32_t target, int64_t suppress, uint64_t* trace, int mode,
+                                              int counter_shift) {
+  uint32_t* counter = counters + (g << counter_shift);
+  uint32_t old;
+  if (mode == 0)
+    old = __hip_atomic_fetch_add(counter, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    old = __hip_atomic_fetch_add(counter, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (old + n == target) {
+    if (mode == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (trace) trace[g] = wall_clock64();
+    if (g != suppress) {
+      if (mode == 0)
+        __hip_atomic_fetch_add(&flags[g], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        __hip_atomic_fetch_add(&flags[g], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+// s_waitcnt vmcnt(0): every vector memory operation of this wave, stores
+// included, has completed (for device-scope stores: at device scope).
+__device__ __forceinline__ void wait_stores_complete() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Persistent grid: workgroups claim runs in production order from an atomic
+// ticket (ticket[0]).  The leading barrier makes sure every wave is done with
+// the previous run (its LDS tile and the broadcast slot) before the slot is
+// rewritten.
+__device__ __forceinline__ int64_t draw_run(uint32_t* ticket, uint32_t* s_tick) {
+  __syncthreads();
+  if (threadIdx.x == 0) *s_tick = __hip_atomic_fetch_add(&ticket[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return (int64_t)__builtin_amdgcn_readfirstlane(*s_tick);
+}
+
+// A workgroup whose draw came back past the last run counts itself out in
+// ticket[1]; the last one re-arms both words for the next launch.  Every
+// workgroup's final draw has returned (its value decided the exit) before it
+// counts itself out, so no draw of this launch can follow the re-arm.
+__device__ __forceinline__ void leave_runs(uint32_t* ticket) {
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(&ticket[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+    __hip_atomic_store(&ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&ticket[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// One workgroup per run of up to K consecutive samples of one table inside one
+// slice.  The counter it feeds is the slice's (target C * T bags)
+// or, with per-table slices, the (slice, table) pair's (target C bags).  Wave
+// w pools a contiguous block of the run's bags: it reads the block's CSR
+// offsets (one lane each), stages the block's whole index segment into its
+// LDS slot when it fits (else bag by bag, SEGW at a time), then gathers every
+// bag into the run's LDS tile.  Rows of more than 64 vectors are pooled 64
+// vectors at a time and stored directly.
+template <class E, int U, bool WT, bool NT, bool FUSED, bool ANY>
+__device__ __forceinline__ void pool_body() {
+  constexpr int EPV = E::EPV;
+  typedef std::conditional_t<ANY, AnyTable<EPV, NT, FUSED>, FastTable<EPV, NT>> Table;
+  extern __shared__ int32_t s_dyn[];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int W = late_args().waves;
+  // LDS: the run's arrival counter and the ticket's broadcast slot, a staging
+  // slot per wave (and one for the weights), the run's pooled rows (K x max
+  // dim floats), with mean pooling their K bag lengths.
+  int32_t* s_arrive = s_dyn;
+  uint32_t* s_tick = reinterpret_cast<uint32_t*>(s_dyn + 1);
+  int32_t* slot = s_dyn + 4 + wid * kPoolSlotWords * (WT ? 2 : 1);
+  float* lds_out = reinterpret_cast<float*>(s_dyn + 4 + W * kPoolSlotWords * (WT ? 2 : 1));
+  if (threadIdx.x == 0) *s_arrive = 0;
+  __syncthreads();
+  // One-shot grid: workgroup i pools run i.  Persistent grid (fewer
+  // workgroups than runs): runs are claimed from the ticket.
+  const bool persistent = gridDim.x < late_args().nruns;
+  for (uint32_t q = persistent ? draw_run(late_args().ticket, s_tick) : blockIdx.x; q < late_args().nruns;
+       q = persistent ? draw_run(late_args().ticket, s_tick) : 0x7fffffffu) {
+    uint32_t gs, tpos, j;
+    int t, nb, per;
+    int64_t g, b0;
+    {
+      const PoolArgs& a = late_args();
+      run_at(a.ro, q, &gs, &tpos, &j);
+      t = sload(a.tperm, tpos);
+      g = slice_at(a.so, gs);
+      b0 = g * a.C + (int64_t)j * a.K;
+      nb = min(a.K, a.C - (int)j * a.K);
+      per = (int)divide_by(a.by_waves, (uint32_t)(nb + W - 1));
+    }
+    {
+      const PoolArgs& a = late_args();
+      const TabMeta m = load_meta(a.meta + t);
+      const void* tab = sload(a.tables, t);
+      const int64_t nnz = sload(a.offsets, (int64_t)a.T * a.B);
+      const int64_t bag0 = (int64_t)t * a.B + b0;  // the run's first bag
+      const int64_t* offs = a.offsets + bag0;
+      float* lens = lds_out + a.out_floats - ((a.K + 3) & ~3);  // mean pooling
+      const int end = min((wid + 1) * per, nb);
+      float acc[EPV];
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+      for (int blk = wid * per; blk < end; blk += 63) {
+        const int c = min(63, end - blk);
+        // Offsets are clamped into [0, nnz] and each bag into the block's
+        // segment, so malformed CSR input can never drive a read outside the
+        // index array (results are then meaningless but memory-safe).  With
+        // index checks a bag of invalid offsets is empty and reported, and its
+        // block goes bag by bag, which leaves the valid bags beside it whole.
+        const int64_t off = offs[blk + min(lane, c)];
+        const int64_t seg_lo = min(max(sload(offs, blk), (int64_t)0), nnz);
+        const int64_t seg_hi = min(max(sload(offs, blk + c), seg_lo), nnz);
+        bool all = seg_hi - seg_lo <= SEGW;  // the block's lookups fit the staging slot
+        uint64_t invalid = 0;
+        if (Table::CHECKS && a.check) {
+          const int64_t next = __shfl_down(off, 1);
+          const bool ok = off >= 0 && off <= next && next <= nnz;
+          invalid = __ballot(lane < c && !ok);
+          if (lane < c && !ok) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(bag0 + blk + lane));
+          if (invalid) all = false;
+        }
+        if (all) stage_block<WT>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
+        const int64_t rel = min(max(off, seg_lo), seg_hi) - seg_lo;
+        const int64_t len = max((int64_t)__shfl_down(rel, 1) - rel, (int64_t)0);
+        if (a.mean && lane < c) lens[blk + lane] = (float)(int)len;
+        const uint32_t packed = all && lane < c ? (uint32_t)rel << 16 | (uint32_t)len : 0u;
+        for (int col = 0; col < (ANY ? m.vecs : 1); col += 64) {
+          Table tb;
+          if constexpr (ANY) {
+            tb.init(tab, m, col, lane);
+            tb.tile = m.vecs <= 64;
+            tb.lrow = lds_out + blk * m.dim + tb.v * EPV;
+            tb.t = t;
+            tb.bag = b0 + blk;
+            tb.len = lens + blk;
+          } else {
+            tb.init(tab, m, lane);
+            tb.lrow = lds_out + blk * m.dim + (lane & ((1 << tb.vs) - 1)) * EPV;
+          }
+          bool carry = false;
+          int64_t lo = 0, hi = 0;
+          for (int i = 0; i < c;) {
+            bool closes = true;
+            uint32_t bags = packed;
+            if (!all) {  // bag by bag, SEGW lookups at a time
+              if (lo == hi) {
+                lo = sload(offs, blk + i);
+                hi = sload(offs, blk + i + 1);
+                if (!Table::CHECKS || !a.check) {
+                  lo = min(max(lo, seg_lo), seg_hi);
+                  hi = min(max(hi, lo), seg_hi);
+                } else if (invalid >> i & 1u) {
+                  lo = hi = 0;
+                }
+                if (ANY && a.mean && lane == 0) lens[blk + i] = (float)(int)(hi - lo);
+              }
+              const int n = (int)min((int64_t)SEGW, hi - lo);
+              stage_block<WT>(a.indices, a.weights, lo, n, lane, slot);
+              bags = lane == 0 ? n : 0;
+              lo += n;
+              closes = lo == hi;
+            }
+            wave_lds_sync();
+            gather_bags<E, U, WT>(tb, all ? c : 1, bags, slot, lane, closes, acc, Table::CHECKS && a.check ? a.status : nullptr,
+                                  bag0 + blk + i, &carry);
+            wave_lds_sync();
+            if (closes) i += all ? c : 1;
+          }
+        }
+      }
+    }
+    // Directly stored rows of this wave are complete before it arrives.
+    if (ANY) wait_stores_complete();
+    // The last wave to finish its bags writes the whole run from LDS to
+    // global memory and (fused) completes the run for the slice; the other
+    // waves leave at once.  No workgroup barrier, and no store ever sits in
+    // front of a gather load of the same wave.
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(s_arrive, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    old = __builtin_amdgcn_readfirstlane(old);
+    if (old == W - 1) {
+      const PoolArgs& a = late_args();
+      if (lane == 0) __hip_atomic_store(s_arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const int dim = sload(&a.meta[t].dim, 0), col_off = sload(&a.meta[t].col_off, 0);
+      const bool tile = !ANY || sload(&a.meta[t].vecs, 0) <= 64;
+      const int64_t stride = FUSED ? a.sum_dim : dim;
+      float* base = a.out + (FUSED ? col_off : a.B * col_off) + b0 * stride;
+      if (tile)
+        store_rows<!ANY>(lds_out, a.mean ? lds_out + a.out_floats - ((a.K + 3) & ~3) : nullptr, nb, base, stride, dim,
+                         lane, FUSED && a.release_mode == 1);
+      if (FUSED) {
+        if (a.release_mode == 1) wait_stores_complete();
+        if (lane == 0)
+          release_slice(a.counters, a.flags, a.per_table ? g * a.T + t : g, (uint32_t)nb,
+                        a.per_table ? (uint32_t)a.C : (uint32_t)a.C * (uint32_t)a.T, a.suppress, a.trace_release,
+                        a.release_mode, a.counter_shift);
+      }
+    }
+  }
+  if (persistent) leave_runs(late_args().ticket);
+}
+
+// Fused operator: pooled vectors go straight to the send layout and slices
+// are released as they complete.
+template <class E, int U, bool WT, bool NT, bool ANY>
+__global__ __launch_bounds__(1024) void fused_pool_kernel(const PoolArgs a) {
+  pool_body<E, U, WT, NT, true, ANY>();
+}
+
+// Unfused baseline, first kernel: plain per-table EmbeddingBag output.
+template <class E, int U, bool WT, bool NT, bool ANY>
+__global__ __launch_bounds__(1024) void unfused_pool_kernel(const PoolArgs a) {
+  pool_body<E, U, WT, NT, false, ANY>();
+}
+
+template <class E, int U, bool WT, bool NT, bool ANY>
+pool_fn pick_f(const PoolVariant& k) {
+  return k.fused ? &fused_pool_kernel<E, U, WT, NT, ANY> : &unfused_pool_kernel<E, U, WT, NT, ANY>;
+}
+
+template <class E, int U, bool WT, bool ANY>
+pool_fn pick_n(const PoolVariant& k) {
+  return k.stream_rows ? pick_f<E, U, WT, true, ANY>(k) : pick_f<E, U, WT, false, ANY>(k);
+}
+
+template <class E, int U, bool WT>
+pool_fn pick_t(const PoolVariant& k) {
+  return k.any ? pick_n<E, U, WT, true>(k) : pick_n<E, U, WT, false>(k);
+}
+
+template <class E>
+pool_fn pick_u(const PoolVariant& k) {
+  switch (k.rows_in_flight) {
+    case 4: return k.weighted ? pick_t<E, 4, true>(k) : pick_t<E, 4, false>(k);
+    case 16: return k.weighted ? pick_t<E, 16, true>(k) : pick_t<E, 16, false>(k);
+    default: return k.weighted ? pick_t<E, 8, true>(k) : pick_t<E, 8, false>(k);
+  }
+}
+
+}  // namespace
+}  // namespace ebag

@@ -1,0 +1,123 @@
+"""The pooling kernel for any tables: rows that are no power of two of
+sixteen-byte vectors (groups of lanes left over), rows of more than 64 vectors
+(pooled 64 at a time, stored directly, a narrow last block), bag lengths at the
+edges of a row group, of the loads in flight and of the staging slot, sum,
+weighted sum and mean, element by element against the oracle; and index checks:
+bags of invalid offsets or rows among valid ones, with rows of one vector block
+and of several."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth import device as sdev
+from tests.gpu_util import check_full, make_plan, new_buffers, run, say
+
+pytestmark = pytest.mark.gpu
+
+VECS = [3, 5, 7, 12, 21, 24, 33, 63, 65, 96, 130]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.set_device(0)
+    yield
+    torch.cuda.synchronize()
+
+
+def _inputs(dtype, vecs, L, rows, B, R, C, weighted, seed):
+    elt = 4 if dtype == synth.F32 else 2
+    rng = np.random.default_rng([2305, 6942, 66, seed])
+    off = np.zeros(len(L) + 1, np.int64)
+    off[1:] = np.cumsum(L)
+    idx = rng.integers(0, rows, int(off[-1])).astype(np.int32)
+    tabs = []
+    for v in vecs:
+        x = rng.standard_normal((rows, v * 16 // elt)).astype(np.float32)
+        tabs.append(x if dtype == synth.F32 else x.astype(np.float16) if dtype == synth.F16
+                    else synth.gen.f32_to_bf16_bits(x))
+    wts = rng.random(int(off[-1]), dtype=np.float32) if weighted else None
+    w = synth.Workload("any", 9, len(vecs), (rows,) * len(vecs), tuple(v * 16 // elt for v in vecs), dtype, B, R, C,
+                       "fixed:1", "uniform", weighted, "normal")
+    return synth.Inputs(w, np.asarray(L, np.int64), off, idx, wts, tabs)
+
+
+@pytest.mark.parametrize("mode", ["sum", "weighted", "mean"])
+@pytest.mark.parametrize("kind", ["edges", "slot"])
+@pytest.mark.parametrize("dtype", [synth.F32, synth.F16, synth.BF16])
+def test_any_width(dtype, kind, mode):
+    import torch
+    B, R, C = 42, 2, 21
+    rng = np.random.default_rng([2305, 6942, 67, dtype, kind == "slot"])
+    L = []
+    for v in VECS:
+        G = max(1, 64 // v)
+        L.append(rng.choice([0, 1, G - 1, G, G + 1, 8 * G - 1, 8 * G, 8 * G + 1], B) if kind == "edges"
+                 else rng.choice([0, 1, 127, 129, 511, 512, 513, 700], B))
+    inp = _inputs(dtype, VECS, np.concatenate(L), 90, B, R, C, mode == "weighted", dtype)
+    w = inp.w
+    say("any tables", dtype, kind, mode)
+    dev = sdev.to_device(inp)
+    s64, a64, _ = oracle.pool_inputs(inp, mean=mode == "mean")
+    outs = []
+    for opts in (dict(), dict(bags_per_run=3, waves_per_wg=1, stream_rows=0, check_indices=1),
+                 dict(bags_per_run=21, persistent_wgs_per_cu=1, release_mode=0), dict(rows_in_flight=4)):
+        plan = make_plan(w, pooling_mode=int(mode == "mean"), **opts)
+        for fused in (True, False):
+            send, _, flags = new_buffers(w)
+            run(plan, w, dev, send, flags, fused=fused)
+            torch.cuda.synchronize()
+            got = send.cpu().numpy()
+            check_full(inp, got, s64, a64)
+            assert np.all(flags.cpu().numpy() == 1)
+            outs.append(got)
+        assert plan.status_ex() == (0, -1, 0, -1)
+        plan.close()
+    for o in outs[1:]:
+        assert np.array_equal(o.view(np.uint32), outs[0].view(np.uint32))
+
+
+@pytest.mark.parametrize("what", ["offsets", "rows", "both"])
+@pytest.mark.parametrize("vec", [4, 5, 70])
+def test_invalid_bags_among_valid_ones(vec, what):
+    """Bags of decreasing offsets, offsets past the end and rows out of range
+    are reported (the lowest one) and every other bag is whole; rows out of
+    range are left out of their bag."""
+    import torch
+    B, rows = 40, 50
+    rng = np.random.default_rng([2305, 6942, 68, vec])
+    inp = _inputs(synth.F32, [vec], rng.integers(1, 9, B), rows, B, 1, 20, False, vec)
+    w, off, idx = inp.w, inp.offsets.copy(), inp.indices.copy()
+    nnz = int(off[-1])
+    if what != "rows":
+        off[13] = off[15] + 2   # bag 13 runs backwards, bag 12 takes in the rows up to it
+        off[31] = nnz + 5       # bags 30 and 31 touch an offset past the end
+    bad_rows = []
+    if what != "offsets":
+        bad_rows = [int(inp.offsets[7]), int(inp.offsets[21])]
+        idx[bad_rows[0]], idx[bad_rows[1]] = rows, -1
+    want = np.zeros((B, w.dims[0]), np.float64)
+    bad = []
+    for b in range(B):
+        lo, hi = int(off[b]), int(off[b + 1])
+        if not 0 <= lo <= hi <= nnz:
+            bad.append(b)
+            continue
+        ok = [k for k in range(lo, hi) if 0 <= idx[k] < rows]
+        if len(ok) < hi - lo:
+            bad.append(b)
+        want[b] = inp.host_tables[0][idx[ok]].astype(np.float64).sum(0)
+    say("invalid bags", vec, what, bad)
+    inp2 = synth.Inputs(w, inp.lengths, off, idx, None, inp.host_tables)
+    dev = sdev.to_device(inp2)
+    for opts in (dict(), dict(bags_per_run=1, waves_per_wg=1), dict(bags_per_run=20, waves_per_wg=1)):
+        plan = make_plan(w, check_indices=1, **opts)
+        send, _, flags = new_buffers(w)
+        run(plan, w, dev, send, flags)
+        torch.cuda.synchronize()
+        assert plan.status_ex() == (0, -1, 0, min(bad))
+        # at most 9 + 9 rows of |values| < 8 a bag, rounded once each
+        assert np.abs(send.cpu().numpy() - want).max() <= 18 * 18 * 8 * 2.0 ** -24
+        plan.close()

@@ -3,10 +3,16 @@
 //
 // GEMV: a wave computes rows of its tile; for a row, lane l takes the 16-byte
 // vectors l, l + 64, ... of the row (coalesced non-temporal loads -- the
-// matrix is read once --, UJ per lane and row in flight, RPI rows at a time)
-// and the matching vectors of x from LDS, where the
-// workgroup staged its rank's x once.  Products are accumulated in fp32 per
-// lane and combined with xor shuffles.
+// matrix is read once) and the matching vectors of x.  Sixteen loads are in
+// flight per lane, spread over RPI rows and UJ = 16 / RPI vectors of each:
+// rows of at most 64 (128, 256) vectors take 16 (8, 4) rows at once and keep
+// the lane's vectors of x in registers; rows of at most 32 vectors share a
+// wave's lanes between two or more rows; longer ones stage the rank's x in the
+// workgroup's LDS.  Products are accumulated in fp32 per lane and combined
+// with xor shuffles; the shape changes no sum's order.
+//
+// Where R * P workgroups do not fill the device, each (r, p) is `split` into
+// several that share every tile's rows (launch_split).
 //
 // AllReduce (fused), two-phase direct: workgroup (r, p) stores its partial
 // tiles for owner q into the reduction slots part[r][rows] with device-scope
@@ -31,8 +37,8 @@ namespace ebag {
 namespace {
 
 constexpr int kMaxRanks = 16;
-constexpr int UJ = 4;             // 16-byte loads in flight per lane per row
-constexpr int RPI = 4;            // rows a wave works on at once (RPI * UJ loads in flight per lane)
+constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
+constexpr int kInFlight = 16;      // 16-byte loads in flight per lane
 constexpr int kMaxXBytes = 64 * 1024;
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
@@ -57,7 +63,12 @@ struct GemvArgs {
   int32_t P;
   int32_t TM;
   int32_t comm_aware;
-  int32_t pad;
+  int32_t split;         // workgroups per (r, p), each taking sub_rows rows of every tile
+  int32_t sub_rows;
+  int32_t lanes;         // lanes per row: 64, or less where all rows are shorter
+  // Tiles owned by rank q: [own[q], own[q + 1]); own_mod[q] = own[q] mod P.
+  int32_t own[kMaxRanks + 1];
+  int32_t own_mod[kMaxRanks];
 };
 
 // 16-byte vector of the storage type -> fp32 values.
@@ -116,39 +127,78 @@ __device__ __forceinline__ float load_f32_device(const float* p) {
 // s_waitcnt vmcnt(0): every memory operation of this wave has completed.
 __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Stage x_r (K * elt bytes, a multiple of 16) into LDS.
-__device__ __forceinline__ void stage_x(const char* x, int64_t bytes, u4v* lds_x) {
-  for (int64_t v = threadIdx.x; v * 16 < bytes; v += blockDim.x) lds_x[v] = *(gu4v*)(x + v * 16);
-}
+// How a launch shapes the GEMV: RPI rows at once, the lane's vectors of x in
+// registers (XREG: rows of at most 64 * UJ vectors) or in LDS.
+template <int RPI_, bool XREG_>
+struct Shape {
+  static constexpr int RPI = RPI_;
+  static constexpr int UJ = kInFlight / RPI_;
+  static constexpr bool XREG = XREG_;
+};
 
-// Partial product of rank r for the rows of tile `tile`, stored into
+// The rank's x, as its lanes use it.
+template <class S>
+struct XVec {
+  u4v reg[S::XREG ? S::UJ : 1];
+  const u4v* lds;
+
+  __device__ __forceinline__ void load(const char* x, int V, int lanes, u4v* lds_x) {
+    lds = lds_x;
+    if (S::XREG) {
+      const int l = threadIdx.x & (lanes - 1);
+#pragma unroll
+      for (int u = 0; u < S::UJ; ++u) {
+        reg[u] = u4v{0u, 0u, 0u, 0u};
+        if (u * 64 + l < V) reg[u] = *(gu4v*)(x + (int64_t)(u * 64 + l) * 16);
+      }
+      return;
+    }
+    // eight loads in flight per thread
+    for (int v0 = threadIdx.x; v0 < V; v0 += 8 * blockDim.x) {
+      u4v t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int v = v0 + u * blockDim.x;
+        t[u] = *(gu4v*)(x + (int64_t)(v < V ? v : v0) * 16);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (v0 + u * blockDim.x < V) lds_x[v0 + u * blockDim.x] = t[u];
+    }
+    __syncthreads();
+  }
+  __device__ __forceinline__ u4v at(int u, int v) const { return S::XREG ? reg[u] : lds[v]; }
+};
+
+// Partial product of rank r for rows [lo, hi) of tile `tile`, stored into
 // part[r][rows] (device-scope stores when `device_scope`).
-template <int DT>
-__device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, const u4v* lds_x, bool device_scope) {
+template <int DT, class S>
+__device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int hi, const XVec<S>& x,
+                             bool device_scope) {
+  constexpr int RPI = S::RPI, UJ = S::UJ;
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
   const int64_t row0 = tile * a.TM;
-  const int nrows = (int)min((int64_t)a.TM, a.M - row0);
-  const int per = (nrows + W - 1) / W;
-  const int r0 = wid * per;
-  const int r1 = min(r0 + per, nrows);
-  const int64_t K = a.K[r];
-  const int64_t row_bytes = K * (DT == 0 ? 4 : 2);
+  const int nrows = (int)min((int64_t)hi, a.M - row0) - lo;
+  const int per = (int)((unsigned)(nrows > 0 ? nrows + W - 1 : 0) / (unsigned)W);
+  const int r0 = lo + wid * per;
+  const int r1 = min(r0 + per, lo + nrows);
+  const int64_t row_bytes = a.K[r] * (DT == 0 ? 4 : 2);
   const int V = (int)(row_bytes / 16);
   const char* Ar = a.A[r];
   float* out = a.part + (int64_t)r * a.M + row0;
+  const int L = S::RPI == kInFlight ? a.lanes : 64;  // lanes per row, G rows per load
+  const int G = S::RPI == kInFlight ? 64 / L : 1;
+  const int g = lane / L, l = lane & (L - 1);
   for (int base = r0; base < r1; base += 64) {  // results of up to 64 rows per store
     float res = 0.f;
     const int nb = min(64, r1 - base);
-    for (int k = 0; k < nb; k += RPI) {
-      const char* pr[RPI];
-      bool has[RPI];
-#pragma unroll
-      for (int j = 0; j < RPI; ++j) {
-        has[j] = k + j < nb;
-        pr[j] = Ar + (row0 + base + k + (has[j] ? j : 0)) * row_bytes;
-      }
+    for (int k = 0; k < nb; k += RPI * G) {
+      // The step's rows are contiguous: one descriptor over what is left of
+      // them, so loads past the last row return zeros.
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<char*>(Ar + (row0 + base + k) * row_bytes), 0, (nb - k) * (int)row_bytes, kBufferWord3);
       float acc[RPI];
 #pragma unroll
       for (int j = 0; j < RPI; ++j) acc[j] = 0.f;
@@ -156,55 +206,68 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, const u4v* 
         u4v ra[RPI][UJ];
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
-          const int v = v0 + u * 64 + lane;
+          const int v = v0 + u * 64 + l;
+          const uint32_t off = v < V ? (uint32_t)(v * 16 + g * (int)row_bytes) : 0x80000000u;  // past any row
 #pragma unroll
-          for (int j = 0; j < RPI; ++j) {
-            ra[j][u] = u4v{0u, 0u, 0u, 0u};
-            if (v < V && has[j]) ra[j][u] = __builtin_nontemporal_load((gu4v*)(pr[j] + (int64_t)v * 16));
-          }
+          for (int j = 0; j < RPI; ++j)
+            ra[j][u] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + (uint32_t)(j * G * (int)row_bytes), 0, 2);
         }
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
-          const int v = v0 + u * 64 + lane;
-          if (v < V) {
-            const u4v xv = lds_x[v];
+          const int v = v0 + u * 64 + l;
+          if (S::XREG || v < V) {
+            u4v xv = x.at(u, v);
+            // bf16: widened here, not kept widened (twice the registers)
+            if (DT == 2) asm volatile("" : "+v"(xv));
 #pragma unroll
             for (int j = 0; j < RPI; ++j) acc[j] += dot16<DT>(ra[j][u], xv);
           }
         }
       }
+      // Lanes past the row hold zeros, so rows that share a wave leave out the
+      // levels that would only add those.
 #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) {
+        if (S::RPI == kInFlight && m >= L) continue;
 #pragma unroll
         for (int j = 0; j < RPI; ++j) acc[j] += __shfl_xor(acc[j], m);
       }
+      if (G == 1) {
 #pragma unroll
-      for (int j = 0; j < RPI; ++j)
-        if (has[j] && lane == k + j) res = acc[j];
+        for (int j = 0; j < RPI; ++j)
+          if (lane == k + j) res = acc[j];
+      } else {
+#pragma unroll
+        for (int j = 0; j < RPI; ++j)
+          if (k + j * G + g < nb && l == 0) store_f32(out + base + k + j * G + g, acc[j], device_scope);
+      }
     }
-    if (lane < nb) store_f32(out + base + lane, res, device_scope);
+    if (G == 1 && lane < nb) store_f32(out + base + lane, res, device_scope);
   }
 }
 
-// First tile of the owner block [t0, t1) that physical workgroup p handles.
-__device__ __forceinline__ int64_t first_tile(int64_t t0, int p, int P) {
-  const int64_t m = t0 % P;
-  return t0 + ((p - m) % P + P) % P;
+// First tile of owner q's block that physical workgroup p handles.
+__device__ __forceinline__ int first_tile(const GemvArgs& a, int q, int p) {
+  const int d = p - a.own_mod[q];
+  return a.own[q] + (d < 0 ? d + a.P : d);
 }
-
-// Tiles owned by rank q: [ceil(q * n / R), ceil((q + 1) * n / R)).
-__device__ __forceinline__ int64_t owner_begin(int64_t n, int q, int R) { return (q * n + R - 1) / R; }
 
 // Sum the R partials of owner q's tiles handled by workgroup p (rank order,
 // device-scope loads) and store the result into every rank's output.
 __device__ void reduce_owned(const GemvArgs& a, int q, int p) {
-  const int64_t t0 = owner_begin(a.n_tiles, q, a.R), t1 = owner_begin(a.n_tiles, q + 1, a.R);
-  for (int64_t i = first_tile(t0, p, a.P); i < t1; i += a.P) {
-    const int64_t row0 = i * a.TM;
+  for (int i = first_tile(a, q, p); i < a.own[q + 1]; i += a.P) {
+    const int64_t row0 = (int64_t)i * a.TM;
     const int nrows = (int)min((int64_t)a.TM, a.M - row0);
     for (int k = threadIdx.x; k < nrows; k += blockDim.x) {
+      // every rank's partial in flight before the first is added
+      float part[kMaxRanks];
+#pragma unroll
+      for (int s = 0; s < kMaxRanks; ++s)
+        if (s < a.R) part[s] = load_f32_device(a.part + (int64_t)s * a.M + row0 + k);
       float sum = 0.f;
-      for (int s = 0; s < a.R; ++s) sum += load_f32_device(a.part + (int64_t)s * a.M + row0 + k);
+#pragma unroll
+      for (int s = 0; s < kMaxRanks; ++s)
+        if (s < a.R) sum += part[s];
       for (int r = 0; r < a.R; ++r) store_f32(a.y[r] + row0 + k, sum, true);
     }
   }
@@ -213,36 +276,40 @@ __device__ void reduce_owned(const GemvArgs& a, int q, int p) {
 // Fused kernel, last-arriver reduction (default): workgroup (r, p) computes
 // its partial tiles owner by owner; after each owner's tiles are stored it
 // counts itself in on that owner's counter (q, p), and the workgroup that
-// completes the count -- the last of the R ranks to deliver -- reduces and
-// broadcasts the owner's tiles, then re-arms the counter.  Nobody waits, so
-// the grid needs no co-residency and launches normally.
-template <int DT>
+// completes the count -- the last of the R ranks' (and their splits') to
+// deliver -- reduces and broadcasts the owner's tiles, then re-arms the
+// counter.  Nobody waits, so the grid needs no co-residency and launches
+// normally.
+template <int DT, class S>
 __global__ __launch_bounds__(1024) void gemv_ar_last_arriver_kernel(const GemvArgs a) {
   extern __shared__ u4v lds_x[];
   __shared__ uint32_t s_old;
-  const int r = blockIdx.x / a.P;
-  const int p = blockIdx.x - r * a.P;
-  stage_x(a.x[r], a.K[r] * (DT == 0 ? 4 : 2), lds_x);
-  __syncthreads();
+  const int split = a.split;
+  const int wg = (int)(blockIdx.x / (unsigned)split), part = (int)blockIdx.x - wg * split;
+  const int r = (int)((unsigned)wg / (unsigned)a.P);
+  const int p = wg - r * a.P;
+  const int lo = part * a.sub_rows, hi = min(lo + a.sub_rows, a.TM);
+  XVec<S> x;
+  x.load(a.x[r], (int)(a.K[r] * (DT == 0 ? 4 : 2) / 16), a.lanes, lds_x);
   for (int qi = 0; qi < a.R; ++qi) {
-    const int q = a.comm_aware ? (r + 1 + qi) % a.R : qi;
-    const int64_t t0 = owner_begin(a.n_tiles, q, a.R), t1 = owner_begin(a.n_tiles, q + 1, a.R);
-    const int64_t i0 = first_tile(t0, p, a.P);
+    int q = a.comm_aware ? r + 1 + qi : qi;
+    if (q >= a.R) q -= a.R;
+    const int i0 = first_tile(a, q, p), t1 = a.own[q + 1];
     if (i0 >= t1) {
       // No tile of owner q for workgroup p (on every rank alike): the owner's
       // own workgroup advances the output flag, which has nothing to cover.
-      if (q == r && a.out_flags && threadIdx.x == 0)
+      if (q == r && a.out_flags && threadIdx.x == 0 && part == 0)
         __hip_atomic_fetch_add(&a.out_flags[(int64_t)q * a.P + p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       continue;
     }
-    for (int64_t i = i0; i < t1; i += a.P) partial_tile<DT>(a, r, i, lds_x, true);
+    for (int i = i0; i < t1; i += a.P) partial_tile<DT, S>(a, r, i, lo, hi, x, true);
     // every wave's partial stores complete (device scope) before counting in
     wait_all_memory();
     __syncthreads();
     uint32_t* c = &a.cnt[(int64_t)q * a.P + p];
     if (threadIdx.x == 0) s_old = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (s_old == (uint32_t)a.R - 1) {
+    if (s_old == (uint32_t)(a.R * split) - 1) {
       reduce_owned(a, q, p);
       wait_all_memory();
       __syncthreads();
@@ -257,20 +324,22 @@ __global__ __launch_bounds__(1024) void gemv_ar_last_arriver_kernel(const GemvAr
   }
 }
 
-template <int DT>
+template <int DT, class S>
 __global__ __launch_bounds__(1024) void gemv_ar_fused_kernel(const GemvArgs a) {
   extern __shared__ u4v lds_x[];
   __shared__ int s_bad;
-  const int r = blockIdx.x / a.P;
-  const int p = blockIdx.x - r * a.P;
-  stage_x(a.x[r], a.K[r] * (DT == 0 ? 4 : 2), lds_x);
+  const int r = (int)(blockIdx.x / (unsigned)a.P);
+  const int p = (int)blockIdx.x - r * a.P;
+  XVec<S> x;
+  x.load(a.x[r], (int)(a.K[r] * (DT == 0 ? 4 : 2) / 16), a.lanes, lds_x);
   if (threadIdx.x == 0) s_bad = 0;
   __syncthreads();
   // Phase 1: partial tiles, other owners first (comm-aware) or in owner order.
   for (int qi = 0; qi < a.R; ++qi) {
-    const int q = a.comm_aware ? (r + 1 + qi) % a.R : qi;
-    const int64_t t0 = owner_begin(a.n_tiles, q, a.R), t1 = owner_begin(a.n_tiles, q + 1, a.R);
-    for (int64_t i = first_tile(t0, p, a.P); i < t1; i += a.P) partial_tile<DT>(a, r, i, lds_x, true);
+    int q = a.comm_aware ? r + 1 + qi : qi;
+    if (q >= a.R) q -= a.R;
+    const int t1 = a.own[q + 1];
+    for (int i = first_tile(a, q, p); i < t1; i += a.P) partial_tile<DT, S>(a, r, i, 0, a.TM, x, true);
     if (q != r) {
       // every wave's partial stores done (device scope) before the flag
       wait_all_memory();
@@ -311,15 +380,17 @@ __global__ __launch_bounds__(1024) void gemv_ar_fused_kernel(const GemvArgs a) {
   }
 }
 
-// Baseline, first kernel: one workgroup per (rank, tile).
-template <int DT>
+// Baseline, first kernel: `split` workgroups per (rank, tile).
+template <int DT, class S>
 __global__ __launch_bounds__(1024) void gemv_partial_kernel(const GemvArgs a) {
   extern __shared__ u4v lds_x[];
-  const int r = blockIdx.x / a.n_tiles;
-  const int64_t tile = blockIdx.x - (int64_t)r * a.n_tiles;
-  stage_x(a.x[r], a.K[r] * (DT == 0 ? 4 : 2), lds_x);
-  __syncthreads();
-  partial_tile<DT>(a, r, tile, lds_x, false);
+  const int wg = (int)(blockIdx.x / (unsigned)a.split), part = (int)blockIdx.x - wg * a.split;
+  const int r = (int)((unsigned)wg / (unsigned)a.n_tiles);
+  const int tile = wg - r * (int)a.n_tiles;
+  const int lo = part * a.sub_rows, hi = min(lo + a.sub_rows, a.TM);
+  XVec<S> x;
+  x.load(a.x[r], (int)(a.K[r] * (DT == 0 ? 4 : 2) / 16), a.lanes, lds_x);
+  partial_tile<DT, S>(a, r, tile, lo, hi, x, false);
 }
 
 // Baseline, second kernel: the AllReduce after the kernel boundary -- every
@@ -339,15 +410,33 @@ __global__ __launch_bounds__(256) void bump_flags_kernel(uint32_t* flags, int64_
 
 typedef void (*gemv_fn)(const GemvArgs);
 
-gemv_fn fused_fn(int dt) {
-  return dt == 0 ? gemv_ar_fused_kernel<0> : dt == 1 ? gemv_ar_fused_kernel<1> : gemv_ar_fused_kernel<2>;
+enum { GEMV_LAST_ARRIVER = 0, GEMV_OWNER_WAITS = 1, GEMV_PARTIAL = 2 };
+
+template <int DT, class S>
+gemv_fn pick_kernel(int which) {
+  return which == GEMV_LAST_ARRIVER ? gemv_ar_last_arriver_kernel<DT, S>
+         : which == GEMV_OWNER_WAITS ? gemv_ar_fused_kernel<DT, S> : gemv_partial_kernel<DT, S>;
 }
-gemv_fn last_arriver_fn(int dt) {
-  return dt == 0 ? gemv_ar_last_arriver_kernel<0>
-                 : dt == 1 ? gemv_ar_last_arriver_kernel<1> : gemv_ar_last_arriver_kernel<2>;
+
+template <int DT>
+gemv_fn pick_shape(int which, int rpi, bool xreg) {
+  if (xreg) {
+    switch (rpi) {
+      case 16: return pick_kernel<DT, Shape<16, true>>(which);
+      case 8: return pick_kernel<DT, Shape<8, true>>(which);
+      default: return pick_kernel<DT, Shape<4, true>>(which);
+    }
+  }
+  switch (rpi) {
+    case 1: return pick_kernel<DT, Shape<1, false>>(which);
+    case 2: return pick_kernel<DT, Shape<2, false>>(which);
+    default: return pick_kernel<DT, Shape<4, false>>(which);
+  }
 }
-gemv_fn partial_fn(int dt) {
-  return dt == 0 ? gemv_partial_kernel<0> : dt == 1 ? gemv_partial_kernel<1> : gemv_partial_kernel<2>;
+
+gemv_fn pick(int dt, int which, int rpi, bool xreg) {
+  return dt == 0 ? pick_shape<0>(which, rpi, xreg)
+                 : dt == 1 ? pick_shape<1>(which, rpi, xreg) : pick_shape<2>(which, rpi, xreg);
 }
 
 }  // namespace
@@ -370,12 +459,18 @@ struct gemv_ar_plan {
   int32_t P = 0;
   int32_t block = 0;
   int32_t resident = 0;  // workgroups the device holds at once for the fused kernel
+  int32_t split = 1;      // workgroups per (r, p) of the last-arriver kernel
+  int32_t sub_rows = 0;
+  int32_t lanes = 64;
+  int rpi = 4;
+  bool xreg = false;
   uint32_t epoch = 0;
   // The last forward's completion, for refusing a forward on another stream
   // while it still runs (the reduction slots and counters are shared).
   hipEvent_t fwd_done = nullptr;
   hipStream_t fwd_stream = nullptr;
   bool fwd_pending = false;
+  size_t lds_bytes() const { return xreg ? 0 : (size_t)max_x_bytes; }
   float* d_part = nullptr;
   uint32_t* d_peer = nullptr;
   uint32_t* d_cnt = nullptr;
@@ -432,6 +527,41 @@ int note_forward(gemv_ar_plan* h, hipStream_t stream) {
   return EBAG_OK;
 }
 
+// Rows at once, and where x lies, by the longest rank's row of V vectors: the
+// rows that fill the loads in flight, so that a wave of short rows does not run
+// with a few lanes or a few loads of the sixteen.  Measured, before (4 rows x 4
+// vectors, x in LDS) and now: 4 ranks x 30000 x 96 bf16 32.8 us and 20.7 us; 8
+// x 8192 x 1024 fp16 33.5 and 28.9; 4 x 65536 x 2048 fp16 (4 rows x 4 vectors
+// still, x in registers) 165.9 and 164.8, 6.5 TB/s, the streaming read ceiling.
+void launch_shape(gemv_ar_plan* h) {
+  const int64_t V = h->max_x_bytes / 16;
+  h->xreg = V <= 256;
+  h->rpi = V <= 64 ? 16 : V <= 128 ? 8 : 4;
+  h->lanes = 64;
+  while (h->lanes > 1 && V <= h->lanes / 2) h->lanes /= 2;
+  // Long rows, fewer than four of them for each of 2048 waves: fewer rows at
+  // once, more of each.
+  if (!h->xreg)
+    while (h->rpi > 1 && (int64_t)h->R * h->M < (int64_t)h->rpi * 2048) h->rpi /= 2;
+}
+
+// Workgroups per (r, p): about kTargetWaves wavefronts in all, each with at
+// least one row and 4 KiB of the matrix per tile.  At 2048 waves of 16 KiB in
+// flight the device has 32 MiB on the way; more of them (4096, 8192) were no
+// faster and at 1 x 4096 x 4096 bf16 slower (17.0, 23.6, 23.3 us; unsplit 36.7),
+// fewer leave small M idle: 1 x 3233 x 8096 fp32 (51 tiles) took 92 us unsplit
+// and takes 28 us, 1 x 256 x 8192 fp32 82 us and 15 us.
+constexpr int64_t kTargetWaves = 2048;
+void launch_split(gemv_ar_plan* h) {
+  const int64_t W = h->opts.waves_per_wg, TM = h->opts.tile_rows;
+  const int64_t min_rows = h->max_x_bytes >= 4096 ? 1 : 4096 / h->max_x_bytes;
+  int64_t split = kTargetWaves / ((int64_t)h->R * h->P * W);
+  if (split > TM / (W * min_rows)) split = TM / (W * min_rows);
+  if (split < 1) split = 1;
+  h->sub_rows = (int32_t)((TM + split - 1) / split);
+  h->split = (int32_t)((TM + h->sub_rows - 1) / h->sub_rows);
+}
+
 int fill_args(gemv_ar_plan* h, const void* const* A, const void* const* x, float* const* y, uint32_t* out_flags,
               GemvArgs* a) {
   if (!h) return fail(EBAG_EINVAL, "null plan");
@@ -461,6 +591,11 @@ int fill_args(gemv_ar_plan* h, const void* const* A, const void* const* x, float
   a->P = h->P;
   a->TM = h->opts.tile_rows;
   a->comm_aware = h->opts.comm_aware;
+  a->split = 1;
+  a->sub_rows = a->TM;
+  a->lanes = h->lanes;
+  for (int q = 0; q <= h->R; ++q) a->own[q] = (int32_t)((q * h->n_tiles + h->R - 1) / h->R);
+  for (int q = 0; q < h->R; ++q) a->own_mod[q] = a->own[q] % h->P;
   return EBAG_OK;
 }
 
@@ -532,10 +667,12 @@ int gemv_ar_create(gemv_ar_t* out, int32_t R, int64_t M, const int64_t* K, int32
       khz > 0)
     h->ticks_per_us = khz / 1000.0;
   const bool owner_mode = o.reduce_mode == 1;
+  launch_shape(h);
   int per_cu = 0;
   if (e == hipSuccess)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, owner_mode ? fused_fn(h->dtype) : last_arriver_fn(h->dtype), h->block, (size_t)max_x);
+        &per_cu, pick(h->dtype, owner_mode ? GEMV_OWNER_WAITS : GEMV_LAST_ARRIVER, h->rpi, h->xreg), h->block,
+        h->lds_bytes());
   if (e != hipSuccess) {
     free_gemv(h);
     return hipf(e, "query device");
@@ -554,6 +691,7 @@ int gemv_ar_create(gemv_ar_t* out, int32_t R, int64_t M, const int64_t* K, int32
     return rc;
   }
   h->P = (int32_t)P;
+  launch_split(h);
 #define GEMV_TRY(call, what)        \
   do {                              \
     hipError_t e_ = (call);         \
@@ -593,16 +731,18 @@ int gemv_ar_forward(gemv_ar_t h, const void* const* A, const void* const* x, flo
   if (++h->epoch == 0) ++h->epoch;
   a.epoch = h->epoch;
   if (h->opts.reduce_mode == 0) {
-    hipLaunchKernelGGL(last_arriver_fn(h->dtype), dim3((unsigned)(h->R * h->P)), dim3(h->block),
-                       (size_t)h->max_x_bytes, stream, a);
+    a.split = h->split;
+    a.sub_rows = h->sub_rows;
+    hipLaunchKernelGGL(pick(h->dtype, GEMV_LAST_ARRIVER, h->rpi, h->xreg), dim3((unsigned)(h->R * h->P * h->split)),
+                       dim3(h->block), h->lds_bytes(), stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hipf(e, "launch the fused GEMV + AllReduce kernel");
     return note_forward(h, stream);
   }
   void* args[] = {&a};
-  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(fused_fn(h->dtype)),
-                                                  dim3((unsigned)(h->R * h->P)), dim3(h->block), args,
-                                                  (unsigned)h->max_x_bytes, stream);
+  const hipError_t e = hipLaunchCooperativeKernel(
+      reinterpret_cast<const void*>(pick(h->dtype, GEMV_OWNER_WAITS, h->rpi, h->xreg)), dim3((unsigned)(h->R * h->P)),
+      dim3(h->block), args, (unsigned)h->lds_bytes(), stream);
   if (e != hipSuccess) return hipf(e, "cooperative launch of the fused GEMV + AllReduce kernel");
   return note_forward(h, stream);
 }
@@ -616,7 +756,12 @@ int gemv_ar_unfused_forward(gemv_ar_t h, const void* const* A, const void* const
   if (rc) return rc;
   const int64_t g1 = (int64_t)h->R * h->n_tiles;
   if (g1 > INT_MAX) return fail(EBAG_EINVAL, "too many tiles for one launch");
-  hipLaunchKernelGGL(partial_fn(h->dtype), dim3((unsigned)g1), dim3(h->block), (size_t)h->max_x_bytes, stream, a);
+  if (g1 * h->split <= INT_MAX) {
+    a.split = h->split;
+    a.sub_rows = h->sub_rows;
+  }
+  hipLaunchKernelGGL(pick(h->dtype, GEMV_PARTIAL, h->rpi, h->xreg), dim3((unsigned)(g1 * a.split)), dim3(h->block),
+                     h->lds_bytes(), stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hipf(e, "launch GEMV kernel");
   hipLaunchKernelGGL(allreduce_kernel, dim3((unsigned)((h->M + 255) / 256)), dim3(256), 0, stream, a);

@@ -128,9 +128,7 @@ def _check(rc: int):
 
 
 def _addr(x) -> Optional[int]:
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
     return x.data_ptr()
 
@@ -144,41 +142,59 @@ def _stream(stream) -> Optional[int]:
     return stream.cuda_stream
 
 
-def _need(buf, nbytes: int, what: str):
+def _need(buf, nbytes: int, what: str, i: int = 0):
     """A torch tensor passed as a buffer must hold at least nbytes (raw
-    integer addresses are the caller's responsibility)."""
-    if buf is not None and hasattr(buf, "numel") and buf.numel() * buf.element_size() < nbytes:
-        raise ValueError(f"{what} holds {buf.numel() * buf.element_size()} bytes, needs {nbytes}")
+    integer addresses are the caller's responsibility).  what: its name, with a
+    {} for its position i among several."""
+    if buf is None or isinstance(buf, int) or not hasattr(buf, "numel"):
+        return
+    if buf.numel() * buf.element_size() < nbytes:
+        raise ValueError(f"{what.format(i)} holds {buf.numel() * buf.element_size()} bytes, needs {nbytes}")
 
 
 F32 = ("float32",)
 I32 = ("int32",)
 I64 = ("int64",)
 FLAG_TYPES = ("int32", "uint32")
+_DTYPES = {}  # dtype -> its name
 
 
-def _is_tensor(x) -> bool:
-    return x is not None and not isinstance(x, int) and hasattr(x, "is_contiguous")
+def _dtype_name(dt) -> str:
+    name = _DTYPES.get(dt)
+    if name is None:
+        name = _DTYPES[dt] = str(dt).replace("torch.", "")
+    return name
 
 
 def _validate(*specs):
     """Every torch tensor handed to a kernel must be contiguous, of the
-    element type the C ABI reads and on the GPU.  specs: (tensor, name,
-    allowed dtype names or None, element bytes or None); None and raw integer
-    addresses are skipped (those are the caller's responsibility).  Layout and
-    type are checked for every tensor before the device of any."""
-    ts = [sp for sp in specs if _is_tensor(sp[0])]
-    for x, what, kinds, elt in ts:
-        if not x.is_contiguous():
-            raise ValueError(f"{what} must be contiguous")
-        name = str(x.dtype).replace("torch.", "")
-        if kinds is not None and name not in kinds:
-            raise ValueError(f"{what} must be {' or '.join(kinds)}, not {name}")
-        if elt is not None and x.element_size() != elt:
-            raise ValueError(f"{what} must have {elt}-byte elements, not {x.element_size()}-byte {name}")
-    for x, what, _, _ in ts:
-        if x.device.type != "cuda":
-            raise ValueError(f"{what} must be a GPU tensor, not one on {x.device}")
+    element type the C ABI reads and on the GPU.  specs: (tensors, name,
+    allowed dtype names or None, element bytes or None), the name with a {} for
+    a tensor's position among several; None and raw integer addresses are
+    skipped (those are the caller's responsibility).  Layout and type are
+    checked for every tensor before the device of any.  The checks run on every
+    call, a few hundred tensors of them for a large plan: names are put together
+    only for an error."""
+    off_gpu = None
+    for xs, what, kinds, elt in specs:
+        for i, x in enumerate(xs):
+            if x is None or isinstance(x, int):
+                continue
+            try:
+                contiguous = x.is_contiguous()
+            except AttributeError:
+                continue
+            if not contiguous:
+                raise ValueError(f"{what.format(i)} must be contiguous")
+            if kinds is not None and _dtype_name(x.dtype) not in kinds:
+                raise ValueError(f"{what.format(i)} must be {' or '.join(kinds)}, not {_dtype_name(x.dtype)}")
+            if elt is not None and x.element_size() != elt:
+                raise ValueError(f"{what.format(i)} must have {elt}-byte elements, not {x.element_size()}-byte "
+                                 f"{_dtype_name(x.dtype)}")
+            if off_gpu is None and not x.is_cuda:
+                off_gpu = what.format(i), x.device
+    if off_gpu is not None:
+        raise ValueError(f"{off_gpu[0]} must be a GPU tensor, not one on {off_gpu[1]}")
 
 
 def _elt(dtype) -> int:
@@ -225,9 +241,9 @@ def forward_noalloc(rows, dims, dtype, chunk_samples, tables, indices, offsets, 
     _need(send, 4 * int(B) * sum(int(d) for d in dims), "send buffer")
     _need(flags, 4 * n_flags, "flags")
     _need(offsets, 8 * (T * int(B) + 1), "offsets")
-    _validate(*[(t, f"table {i}", None, _elt(dtype)) for i, t in enumerate(tables)],
-              (indices, "indices", I32, None), (offsets, "offsets", I64, None), (weights, "weights", F32, None),
-              (send, "send buffer", F32, None), (flags, "flags", FLAG_TYPES, None))
+    _validate((tables, "table {}", None, _elt(dtype)), ((indices,), "indices", I32, None),
+              ((offsets,), "offsets", I64, None), ((weights,), "weights", F32, None),
+              ((send,), "send buffer", F32, None), ((flags,), "flags", FLAG_TYPES, None))
     if hasattr(indices, "numel") and indices.numel() == 0:
         raise ValueError("indices must have a device address: pass a one-element buffer when every bag is empty")
     rows_a = (ctypes.c_int64 * T)(*[int(r) for r in rows])
@@ -287,21 +303,17 @@ class Plan:
         _need(send, 4 * int(B) * sum(self.dims), "send buffer")
         _need(flags, 4 * self.n_flags(int(B)), "flags")
 
-    def _offsets(self, B, offsets):
-        _need(offsets, 8 * (self.T * int(B) + 1), "offsets")
-        return _addr(offsets)
-
     def _fwd_types(self, tables, indices, offsets, weights, send, flags):
-        _validate(*[(t, f"table {i}", None, self.elt) for i, t in enumerate(tables)],
-                  (indices, "indices", I32, None), (offsets, "offsets", I64, None), (weights, "weights", F32, None),
-                  (send, "send buffer", F32, None), (flags, "flags", FLAG_TYPES, None))
+        _validate((tables, "table {}", None, self.elt), ((indices,), "indices", I32, None),
+                  ((offsets,), "offsets", I64, None), ((weights,), "weights", F32, None),
+                  ((send,), "send buffer", F32, None), ((flags,), "flags", FLAG_TYPES, None))
 
     def forward(self, tables, indices, offsets, weights, B, R, send, flags, stream=None):
         self._fwd_sizes(B, send, flags)
         _need(offsets, 8 * (self.T * int(B) + 1), "offsets")
         self._fwd_types(tables, indices, offsets, weights, send, flags)
         _check(self._lib.ebag_a2a_forward(self._h, self._tables(tables), self._indices(indices),
-                                          self._offsets(B, offsets), _addr(weights), int(B), int(R), _addr(send),
+                                          _addr(offsets), _addr(weights), int(B), int(R), _addr(send),
                                           _addr(flags), _stream(stream)))
 
     def unfused_forward(self, tables, indices, offsets, weights, B, R, send, flags, stream=None):
@@ -309,30 +321,32 @@ class Plan:
         _need(offsets, 8 * (self.T * int(B) + 1), "offsets")
         self._fwd_types(tables, indices, offsets, weights, send, flags)
         _check(self._lib.ebag_a2a_unfused_forward(self._h, self._tables(tables), self._indices(indices),
-                                                  self._offsets(B, offsets), _addr(weights), int(B), int(R),
+                                                  _addr(offsets), _addr(weights), int(B), int(R),
                                                   _addr(send), _addr(flags), _stream(stream)))
 
     def consume(self, send, flags, recv, B, R, expected_epoch, stream=None):
         self._fwd_sizes(B, send, flags)
         _need(recv, 4 * int(B) * sum(self.dims), "recv buffer")
-        _validate((send, "send buffer", F32, None), (flags, "flags", FLAG_TYPES, None), (recv, "recv buffer", F32, None))
+        _validate(((send,), "send buffer", F32, None), ((flags,), "flags", FLAG_TYPES, None),
+                  ((recv,), "recv buffer", F32, None))
         _check(self._lib.ebag_a2a_consume(self._h, _addr(send), _addr(flags), _addr(recv), int(B), int(R),
                                           int(expected_epoch) & 0xFFFFFFFF, _stream(stream)))
 
     def backward(self, grad, offsets, weights, B, R, values, grad_flags=None, expected_epoch=0, stream=None):
         self._fwd_sizes(B, grad, grad_flags)
         _need(offsets, 8 * (self.T * int(B) + 1), "offsets")
-        _validate((grad, "gradient", F32, None), (grad_flags, "gradient flags", FLAG_TYPES, None),
-                  (offsets, "offsets", I64, None), (weights, "weights", F32, None), (values, "values", F32, None))
+        _validate(((grad,), "gradient", F32, None), ((grad_flags,), "gradient flags", FLAG_TYPES, None),
+                  ((offsets,), "offsets", I64, None), ((weights,), "weights", F32, None),
+                  ((values,), "values", F32, None))
         _check(self._lib.ebag_a2a_backward(self._h, _addr(grad), _addr(grad_flags), int(expected_epoch) & 0xFFFFFFFF,
-                                           self._offsets(B, offsets), _addr(weights), int(B), int(R), _addr(values),
+                                           _addr(offsets), _addr(weights), int(B), int(R), _addr(values),
                                            _stream(stream)))
 
     def deliver(self, src, dst, flags, B, R, stream=None):
         self._fwd_sizes(B, src, flags)
         _need(dst, 4 * int(B) * sum(self.dims), "destination buffer")
-        _validate((src, "source buffer", F32, None), (dst, "destination buffer", F32, None),
-                  (flags, "flags", FLAG_TYPES, None))
+        _validate(((src,), "source buffer", F32, None), ((dst,), "destination buffer", F32, None),
+                  ((flags,), "flags", FLAG_TYPES, None))
         _check(self._lib.ebag_a2a_deliver(self._h, _addr(src), _addr(dst), _addr(flags), int(B), int(R),
                                           _stream(stream)))
 
@@ -405,24 +419,24 @@ class GemvAR:
         _check(lib.gemv_ar_create(ctypes.byref(h), self.R, self.M, ks, int(dtype), ctypes.byref(o)))
         self._h = h
         self._lib = lib
+        self._P = self.launch_info()[0]
+        self._ptrs = ctypes.c_void_p * self.R
 
     def _arrays(self, A, x, y):
         if not (len(A) == len(x) == len(y) == self.R):
             raise ValueError(f"expected {self.R} buffers each for A, x and y")
         for r in range(self.R):
-            _need(A[r], self.M * self.K[r] * self.elt, f"A[{r}]")
-            _need(x[r], self.K[r] * self.elt, f"x[{r}]")
-        _validate(*[(A[r], f"A[{r}]", None, self.elt) for r in range(self.R)],
-                  *[(x[r], f"x[{r}]", None, self.elt) for r in range(self.R)],
-                  *[(y[r], f"y[{r}]", F32, None) for r in range(self.R)])
-        arr = ctypes.c_void_p * self.R
+            _need(A[r], self.M * self.K[r] * self.elt, "A[{}]", r)
+            _need(x[r], self.K[r] * self.elt, "x[{}]", r)
+        _validate((A, "A[{}]", None, self.elt), (x, "x[{}]", None, self.elt), (y, "y[{}]", F32, None))
+        arr = self._ptrs
         return arr(*[_addr(a) for a in A]), arr(*[_addr(v) for v in x]), arr(*[_addr(v) for v in y])
 
     def _out_sizes(self, y, out_flags):
         for v in y:
             _need(v, 4 * self.M, "output vector")
-        _need(out_flags, 4 * self.R * self.launch_info()[0], "out_flags")
-        _validate((out_flags, "out_flags", FLAG_TYPES, None))
+        _need(out_flags, 4 * self.R * self._P, "out_flags")
+        _validate(((out_flags,), "out_flags", FLAG_TYPES, None))
 
     def forward(self, A, x, y, out_flags=None, stream=None):
         self._out_sizes(y, out_flags)

@@ -20,6 +20,7 @@ struct BackwardArgs {
   int64_t nruns;
   uint64_t timeout_ticks;
   SliceOrder so;
+  RunOrder ro;
   int32_t T;
   int32_t C;
   int32_t K;
@@ -29,7 +30,7 @@ struct BackwardArgs {
   int32_t per_table;
   int32_t mean;
   uint32_t epoch;
-  int32_t pad;
+  int32_t w_slots;            // LDS words for the run's weights (0 without weights)
 };
 
 // One-GPU stand-in for the gradient All-to-All's arrival.

@@ -58,15 +58,92 @@ __global__ __launch_bounds__(256) void value_base_kernel(const int64_t* offsets,
   if (tid == 0) base[T] = carry;
 }
 
+// Streams a run's output block, n = rows x V float4s, to out: element e is
+// vector e mod V of lookup e / V, the row of the lookup's bag times its weight.
+// Each thread walks elements tid, tid + step, ... keeping its (lookup, vector)
+// position incrementally (no division on the way) and the end of its current
+// bag in a register (LDS is read only when a bag boundary is crossed).
+//
+// The weights lie in LDS (LDSW) wherever the run's fit its slots.  Loads and
+// stores are counted by one counter on this GPU, in order, so a weight loaded
+// from memory on the way cannot be waited for without the stores before it.
+template <class I, bool WT, bool LDSW>
+struct BlockStream {
+  const f4v* rows_lds;
+  const int64_t* s_off;
+  const float* w;
+  f4v* out;
+  I n, k, bag_end;
+  int V, step, dk, dc, c, bag;
+
+  // UB elements from e0 on: their LDS rows and weights are all requested before
+  // the first store.
+  template <int UB>
+  __device__ __forceinline__ void pass(I e0) {
+    f4v x[UB];
+    float wv[UB];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const bool in = e0 + (I)u * step < n;
+      // k < rows = s_off[nb] for every element in range, so the walk stops
+      // at a bag below nb.
+      if (in)
+        while (k >= bag_end) bag_end = (I)s_off[++bag + 1];
+      x[u] = rows_lds[bag * V + c];
+      wv[u] = WT ? (LDSW ? w[in ? k : 0] : in ? w[k] : 1.f) : 1.f;
+      k += dk;
+      c += dc;
+      if (c >= V) {
+        c -= V;
+        ++k;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+      if (e0 + (I)u * step < n) __builtin_nontemporal_store(WT ? wv[u] * x[u] : x[u], out + e0 + (I)u * step);
+  }
+
+  // Eight elements a thread at a time while more than four are left, then as
+  // few as hold the rest.  Measured, 4 at a time always and like this: 48 tables
+  // of 32 to 256 floats, weighted bags of 1 to 100 (9.8 GB) 1768 us and 1706 us;
+  // 32 x 128 floats, bags of 40 (10.9 GB) 1918 and 1844; bags of 32 at 4 a run,
+  // four elements a thread, 340 and 345 (level within its runs overlapped with
+  // the delivery).  Eight-element passes over a rest of three or four made the
+  // weighted ones 15% slower.
+  __device__ __forceinline__ void run() {
+    dk = (int)((unsigned)step / (unsigned)V);
+    dc = step - dk * V;
+    k = (I)((unsigned)threadIdx.x / (unsigned)V);
+    c = (int)threadIdx.x - (int)k * V;
+    bag = 0;
+    bag_end = (I)s_off[1];
+    for (I e = 0; e < n;) {
+      const I left = n - e;
+      if (left > (I)4 * step) {
+        pass<8>(e + (I)threadIdx.x);
+        e += (I)8 * step;
+      } else {
+        if (left > (I)2 * step)
+          pass<4>(e + (I)threadIdx.x);
+        else if (left > step)
+          pass<2>(e + (I)threadIdx.x);
+        else
+          pass<1>(e + (I)threadIdx.x);
+        break;
+      }
+    }
+  }
+};
+
+template <bool WT>
 __global__ __launch_bounds__(1024) void backward_kernel(const BackwardArgs a) {
-  // LDS: the run's K scaled gradient rows [K][dim], then its K + 1 bag
-  // offsets relative to the run's first lookup.
+  // LDS: the run's K scaled gradient rows [K][dim], its K + 1 bag offsets
+  // relative to the run's first lookup, its weights.
   extern __shared__ f4v s_lds[];
   __shared__ int s_bad;
   const int tid = threadIdx.x;
-  int64_t gs;
-  int32_t tpos, j;
-  run_at(a.so, a.T, a.J, blockIdx.x, &gs, &tpos, &j);
+  uint32_t gs, tpos, j;
+  run_at(a.ro, blockIdx.x, &gs, &tpos, &j);
   const int t = sld(a.tperm, tpos);
   const int64_t g = slice_at(a.so, gs);
   if (a.flags) {
@@ -92,70 +169,56 @@ __global__ __launch_bounds__(1024) void backward_kernel(const BackwardArgs a) {
   const int col_off = sld(&a.meta[t].col_off, 0);
   const int V = dim >> 2;  // float4 per row
   const int64_t b0 = g * a.C + (int64_t)j * a.K;
-  const int nb = (int)min((int64_t)a.K, (g + 1) * (int64_t)a.C - b0);
+  const int nb = min(a.K, a.C - (int)j * a.K);
   const int64_t obase = (int64_t)t * a.B + b0;
   const int64_t lo0 = sld(a.offsets, obase);
+  const int64_t rows = sld(a.offsets, obase + nb) - lo0;
+  const int64_t table_lo = sld(a.offsets, (int64_t)t * a.B);
+  const int64_t base = sld(a.value_base, t);
   int64_t* s_off = reinterpret_cast<int64_t*>(s_lds + (int64_t)a.K * (a.max_dim >> 2));
+  float* s_w = reinterpret_cast<float*>(s_off + a.K + 1);
+  const bool lds_w = WT && rows <= a.w_slots;
+  // A run of a few lookups takes no more waves than its output, its gradient
+  // rows and its offsets need; the others leave before the barrier, and their
+  // slots take the next workgroup's (26 tables x 16384 bags of 0 to 3 lookups of
+  // 128 floats: 522 us before, 486 us without this, 413 us with it).
+  const int64_t n = rows * V;
+  int step = blockDim.x;
+  {
+    const int64_t most = max(max(n, (int64_t)nb * V), (int64_t)nb + 1);
+    if (most < step) step = ((int)most + 63) & ~63;
+    if (tid >= step) return;
+  }
   if (tid <= nb) s_off[tid] = a.offsets[obase + tid] - lo0;
+  if (lds_w)
+    for (int i = tid; i < (int)rows; i += step) s_w[i] = a.weights[lo0 + i];
   // the run's gradient rows, scaled once (device-scope loads: with flags the
   // rows were stored by a kernel that may still be running)
-  float* s_rows = reinterpret_cast<float*>(s_lds);
-  for (int e = tid; e < nb * dim; e += blockDim.x) {
-    const int k = e / dim;
-    const int c = e - k * dim;
-    const float* gp = a.grad + (b0 + k) * a.sum_dim + col_off + c;
-    float v = a.flags ? __hip_atomic_load(const_cast<float*>(gp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *gp;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(a.grad + b0 * a.sum_dim + col_off), 0, ((nb - 1) * a.sum_dim + dim) * 4, 0x00020000);
+  for (int e = tid; e < nb * V; e += step) {
+    const int k = (int)((unsigned)e / (unsigned)V);
+    const int off = (k * a.sum_dim + (e - k * V) * 4) * 4;
+    const u4v r = a.flags ? __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 16)
+                          : __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+    f4v v = {__uint_as_float(r.x), __uint_as_float(r.y), __uint_as_float(r.z), __uint_as_float(r.w)};
     if (a.mean) {
-      const int64_t L = a.offsets[obase + k + 1] - a.offsets[obase + k];
-      v = v / (float)L;
+      const float L = (float)(a.offsets[obase + k + 1] - a.offsets[obase + k]);
+      v = f4v{v.x / L, v.y / L, v.z / L, v.w / L};
     }
-    s_rows[k * dim + c] = v;
+    s_lds[e] = v;
   }
   __syncthreads();
   // The run's output is one contiguous block of (lookups of its bags) x dim
-  // floats; the whole workgroup streams it out.  Each thread walks float4
-  // elements tid, tid + blockDim, ... keeping its (row, vector) position
-  // incrementally (no division inside the loop) and the end of its current
-  // bag in a register (LDS is read only when a bag boundary is crossed).
-  // Four elements at a time: their LDS rows and weights are all requested
-  // before the first store.
-  const int64_t rows = s_off[nb];
-  const int64_t n = rows * V;
-  f4v* out = reinterpret_cast<f4v*>(a.values + sld(a.value_base, t) + (lo0 - sld(a.offsets, (int64_t)t * a.B)) * dim);
-  const int step = blockDim.x;
-  const int dk = step / V, dc = step - (step / V) * V;
-  int64_t k = tid / V;
-  int c = tid - (tid / V) * V;
-  int bag = 0;
-  int64_t bag_end = s_off[1];  // nb >= 1
-  const float* wts = a.weights ? a.weights + lo0 : nullptr;
-  constexpr int UB = 4;
-  for (int64_t e0 = tid; e0 < n; e0 += (int64_t)UB * step) {
-    f4v x[UB];
-    float wv[UB];
-#pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const bool in = e0 + (int64_t)u * step < n;
-      // k < rows = s_off[nb] for every element in range, so the walk stops
-      // at a bag below nb.
-      if (in)
-        while (k >= bag_end) bag_end = s_off[++bag + 1];
-      x[u] = s_lds[bag * V + c];
-      wv[u] = wts && in ? wts[k] : 1.f;
-      k += dk;
-      c += dc;
-      if (c >= V) {
-        c -= V;
-        ++k;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      if (e0 + (int64_t)u * step < n) {
-        const f4v y = wts ? wv[u] * x[u] : x[u];
-        __builtin_nontemporal_store(y, out + e0 + (int64_t)u * step);
-      }
-    }
+  // floats; the whole workgroup streams it out.
+  f4v* out = reinterpret_cast<f4v*>(a.values + base + (lo0 - table_lo) * dim);
+  if (n < 0x20000000) {
+    if (!WT || lds_w)
+      BlockStream<int, WT, true>{s_lds, s_off, s_w, out, (int)n, 0, 0, V, step}.run();
+    else
+      BlockStream<int, WT, false>{s_lds, s_off, a.weights + lo0, out, (int)n, 0, 0, V, step}.run();
+  } else {
+    BlockStream<int64_t, WT, false>{s_lds, s_off, WT ? a.weights + lo0 : nullptr, out, n, 0, 0, V, step}.run();
   }
 }
 
@@ -255,7 +318,8 @@ hipError_t launch_backward(const BackwardArgs& a, int64_t* value_base, int block
   hipLaunchKernelGGL(value_base_kernel, dim3(1), dim3(256), 0, stream, a.offsets, a.meta, a.T, a.B, value_base);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(backward_kernel, dim3((unsigned)a.nruns), dim3(block), lds, stream, a);
+  hipLaunchKernelGGL(a.weights ? backward_kernel<true> : backward_kernel<false>, dim3((unsigned)a.nruns), dim3(block),
+                     lds, stream, a);
   return hipGetLastError();
 }
 

@@ -644,9 +644,12 @@ int ebag_a2a_backward(ebag_a2a_t h, const float* grad_buf, const uint32_t* grad_
   if (k_fit < 1) return fail(EBAG_EUNSUPPORTED, "backward: rows of %d floats do not fit in LDS", max_dim);
   if (K > k_fit) K = k_fit;
   if (K > block - 1) K = block - 1;
-  const size_t lds = (size_t)K * max_dim * sizeof(float) + (size_t)(K + 1) * sizeof(int64_t);
   BackwardArgs a;
   std::memset(&a, 0, sizeof a);
+  // Weighted: 8 KiB for the run's weights (eight bags of 250 lookups); longer
+  // runs read theirs from memory.
+  a.w_slots = weights ? 2048 : 0;
+  const size_t lds = (size_t)K * max_dim * sizeof(float) + (size_t)(K + 1) * sizeof(int64_t) + a.w_slots * sizeof(float);
   a.grad = grad_buf;
   a.flags = grad_flags;
   a.values = values;
@@ -665,6 +668,7 @@ int ebag_a2a_backward(ebag_a2a_t h, const float* grad_buf, const uint32_t* grad_
   a.J = (h->C + a.K - 1) / a.K;
   a.nruns = so.n_chunks * (int64_t)h->T * a.J;
   if (a.nruns >= INT_MAX) return fail(EBAG_EINVAL, "too many runs (%lld) for one launch", (long long)a.nruns);
+  a.ro = make_run_order(so, h->T, a.J);
   a.sum_dim = h->sum_dim;
   a.max_dim = max_dim;
   a.per_table = h->opts.slice_granule == 1;

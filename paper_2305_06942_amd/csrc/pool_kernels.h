@@ -429,6 +429,7 @@ __device__ __forceinline__ void gather_bags(Table& tb, int c, uint32_t bags, con
       if (cnt[u] > 0) {  // empty bags and the block's end skip
         bool bad = false;
         raw[u] = tb.load(r[u], cnt[u], &bad);
+        if (Table::CHECKS && WT) wv[u] = bad ? 0.f : wv[u];  // left out, whatever its weight
         if (Table::CHECKS && status) bads |= __any(bad) ? 1u << u : 0u;
       }
     }

@@ -121,3 +121,29 @@ def test_invalid_bags_among_valid_ones(vec, what):
         # at most 9 + 9 rows of |values| < 8 a bag, rounded once each
         assert np.abs(send.cpu().numpy() - want).max() <= 18 * 18 * 8 * 2.0 ** -24
         plan.close()
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.F16, synth.BF16])
+@pytest.mark.parametrize("vec", [4, 5, 70])
+def test_rows_left_out_whatever_their_weight(vec, dtype):
+    """A row out of range adds nothing to its bag, also where its weight is
+    infinite or not a number."""
+    import torch
+    B, rows = 24, 50
+    rng = np.random.default_rng([2305, 6942, 69, vec, dtype])
+    inp = _inputs(dtype, [vec], rng.integers(1, 9, B), rows, B, 1, 12, True, vec)
+    left_out = _inputs(dtype, [vec], inp.lengths, rows, B, 1, 12, True, vec)
+    assert np.array_equal(inp.indices, left_out.indices)
+    for b, (row, weight) in {3: (rows, np.inf), 11: (-1, np.nan), 19: (rows + 7, -np.inf)}.items():
+        k = int(inp.offsets[b])
+        inp.indices[k], inp.weights[k] = row, weight
+        left_out.indices[k], left_out.weights[k] = 0, 0.0
+    say("rows left out", vec, dtype)
+    dev = sdev.to_device(inp)
+    plan = make_plan(inp.w, check_indices=1)
+    send, _, flags = new_buffers(inp.w)
+    run(plan, inp.w, dev, send, flags)
+    torch.cuda.synchronize()
+    assert plan.status_ex() == (0, -1, 0, 3)
+    check_full(left_out, send.cpu().numpy())
+    plan.close()

@@ -147,3 +147,31 @@ def test_rows_left_out_whatever_their_weight(vec, dtype):
     assert plan.status_ex() == (0, -1, 0, 3)
     check_full(left_out, send.cpu().numpy())
     plan.close()
+
+
+@pytest.mark.parametrize("vec", [3, 6, 12, 20, 24])
+def test_short_weighted_bags_add_in_sequence(vec):
+    """Weighted bags of fewer than seven lookups of a table whose rows are no
+    power of two of vectors: fma(w, x, sum) row after row, bit for bit.  In 64
+    bits a product and its sum with the one before are exact here: weights are
+    multiples of 2^-24, fp16 values of 2^-24, sums stay below 2^5."""
+    import torch
+    B, rows = 56, 50
+    L = np.tile(np.arange(8), 7)
+    inp = _inputs(synth.F16, [vec], L, rows, B, 1, 28, True, vec)
+    say("short weighted bags", vec)
+    dev = sdev.to_device(inp)
+    plan = make_plan(inp.w)
+    send, _, flags = new_buffers(inp.w)
+    run(plan, inp.w, dev, send, flags)
+    torch.cuda.synchronize()
+    got = send.cpu().numpy()
+    tab = inp.host_tables[0].astype(np.float64)
+    for b in range(B):
+        if L[b] > 6:
+            continue
+        acc = np.zeros(inp.w.dims[0], np.float32)
+        for k in range(int(inp.offsets[b]), int(inp.offsets[b + 1])):
+            acc = (acc.astype(np.float64) + float(inp.weights[k]) * tab[inp.indices[k]]).astype(np.float32)
+        assert np.array_equal(acc.view(np.uint32), got[b].view(np.uint32)), b
+    plan.close()

@@ -12,7 +12,7 @@
 // with xor shuffles; the shape changes no sum's order.
 //
 // Where R * P workgroups do not fill the device, each (r, p) is `split` into
-// several that share every tile's rows (launch_split).
+// several that share every tile's rows (split_for).
 //
 // AllReduce (fused), two-phase direct: workgroup (r, p) stores its partial
 // tiles for owner q into the reduction slots part[r][rows] with device-scope
@@ -32,11 +32,11 @@
 #include "common.h"
 #include "device_guard.h"
 #include "gemv_ar.h"
+#include "gemv_tiles.h"
 
 namespace ebag {
 namespace {
 
-constexpr int kMaxRanks = 16;
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 constexpr int kInFlight = 16;      // 16-byte loads in flight per lane
 constexpr int kMaxXBytes = 64 * 1024;
@@ -66,9 +66,7 @@ struct GemvArgs {
   int32_t split;         // workgroups per (r, p), each taking sub_rows rows of every tile
   int32_t sub_rows;
   int32_t lanes;         // lanes per row: 64, or less where all rows are shorter
-  // Tiles owned by rank q: [own[q], own[q + 1]); own_mod[q] = own[q] mod P.
-  int32_t own[kMaxRanks + 1];
-  int32_t own_mod[kMaxRanks];
+  TileOwners tiles;
 };
 
 // 16-byte vector of the storage type -> fp32 values.
@@ -246,16 +244,10 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int
   }
 }
 
-// First tile of owner q's block that physical workgroup p handles.
-__device__ __forceinline__ int first_tile(const GemvArgs& a, int q, int p) {
-  const int d = p - a.own_mod[q];
-  return a.own[q] + (d < 0 ? d + a.P : d);
-}
-
 // Sum the R partials of owner q's tiles handled by workgroup p (rank order,
 // device-scope loads) and store the result into every rank's output.
 __device__ void reduce_owned(const GemvArgs& a, int q, int p) {
-  for (int i = first_tile(a, q, p); i < a.own[q + 1]; i += a.P) {
+  for (uint32_t i = first_tile(a.tiles, q, p, a.P); i < a.tiles.own[q + 1]; i += a.P) {
     const int64_t row0 = (int64_t)i * a.TM;
     const int nrows = (int)min((int64_t)a.TM, a.M - row0);
     for (int k = threadIdx.x; k < nrows; k += blockDim.x) {
@@ -294,7 +286,7 @@ __global__ __launch_bounds__(1024) void gemv_ar_last_arriver_kernel(const GemvAr
   for (int qi = 0; qi < a.R; ++qi) {
     int q = a.comm_aware ? r + 1 + qi : qi;
     if (q >= a.R) q -= a.R;
-    const int i0 = first_tile(a, q, p), t1 = a.own[q + 1];
+    const uint32_t i0 = first_tile(a.tiles, q, p, a.P), t1 = a.tiles.own[q + 1];
     if (i0 >= t1) {
       // No tile of owner q for workgroup p (on every rank alike): the owner's
       // own workgroup advances the output flag, which has nothing to cover.
@@ -302,7 +294,7 @@ __global__ __launch_bounds__(1024) void gemv_ar_last_arriver_kernel(const GemvAr
         __hip_atomic_fetch_add(&a.out_flags[(int64_t)q * a.P + p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       continue;
     }
-    for (int i = i0; i < t1; i += a.P) partial_tile<DT, S>(a, r, i, lo, hi, x, true);
+    for (uint32_t i = i0; i < t1; i += a.P) partial_tile<DT, S>(a, r, i, lo, hi, x, true);
     // every wave's partial stores complete (device scope) before counting in
     wait_all_memory();
     __syncthreads();
@@ -338,8 +330,8 @@ __global__ __launch_bounds__(1024) void gemv_ar_fused_kernel(const GemvArgs a) {
   for (int qi = 0; qi < a.R; ++qi) {
     int q = a.comm_aware ? r + 1 + qi : qi;
     if (q >= a.R) q -= a.R;
-    const int t1 = a.own[q + 1];
-    for (int i = first_tile(a, q, p); i < t1; i += a.P) partial_tile<DT, S>(a, r, i, 0, a.TM, x, true);
+    const uint32_t t1 = a.tiles.own[q + 1];
+    for (uint32_t i = first_tile(a.tiles, q, p, a.P); i < t1; i += a.P) partial_tile<DT, S>(a, r, i, 0, a.TM, x, true);
     if (q != r) {
       // every wave's partial stores done (device scope) before the flag
       wait_all_memory();
@@ -545,23 +537,6 @@ void launch_shape(gemv_ar_plan* h) {
     while (h->rpi > 1 && (int64_t)h->R * h->M < (int64_t)h->rpi * 2048) h->rpi /= 2;
 }
 
-// Workgroups per (r, p): about kTargetWaves wavefronts in all, each with at
-// least one row and 4 KiB of the matrix per tile.  At 2048 waves of 16 KiB in
-// flight the device has 32 MiB on the way; more of them (4096, 8192) were no
-// faster and at 1 x 4096 x 4096 bf16 slower (17.0, 23.6, 23.3 us; unsplit 36.7),
-// fewer leave small M idle: 1 x 3233 x 8096 fp32 (51 tiles) took 92 us unsplit
-// and takes 28 us, 1 x 256 x 8192 fp32 82 us and 15 us.
-constexpr int64_t kTargetWaves = 2048;
-void launch_split(gemv_ar_plan* h) {
-  const int64_t W = h->opts.waves_per_wg, TM = h->opts.tile_rows;
-  const int64_t min_rows = h->max_x_bytes >= 4096 ? 1 : 4096 / h->max_x_bytes;
-  int64_t split = kTargetWaves / ((int64_t)h->R * h->P * W);
-  if (split > TM / (W * min_rows)) split = TM / (W * min_rows);
-  if (split < 1) split = 1;
-  h->sub_rows = (int32_t)((TM + split - 1) / split);
-  h->split = (int32_t)((TM + h->sub_rows - 1) / h->sub_rows);
-}
-
 int fill_args(gemv_ar_plan* h, const void* const* A, const void* const* x, float* const* y, uint32_t* out_flags,
               GemvArgs* a) {
   if (!h) return fail(EBAG_EINVAL, "null plan");
@@ -594,8 +569,7 @@ int fill_args(gemv_ar_plan* h, const void* const* A, const void* const* x, float
   a->split = 1;
   a->sub_rows = a->TM;
   a->lanes = h->lanes;
-  for (int q = 0; q <= h->R; ++q) a->own[q] = (int32_t)((q * h->n_tiles + h->R - 1) / h->R);
-  for (int q = 0; q < h->R; ++q) a->own_mod[q] = a->own[q] % h->P;
+  make_owners(h->n_tiles, h->R, h->P, &a->tiles);
   return EBAG_OK;
 }
 
@@ -691,7 +665,7 @@ int gemv_ar_create(gemv_ar_t* out, int32_t R, int64_t M, const int64_t* K, int32
     return rc;
   }
   h->P = (int32_t)P;
-  launch_split(h);
+  h->split = split_for((int64_t)R * P, o.waves_per_wg, o.tile_rows, max_x, &h->sub_rows);
 #define GEMV_TRY(call, what)        \
   do {                              \
     hipError_t e_ = (call);         \

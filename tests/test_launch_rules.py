@@ -1,5 +1,5 @@
-"""The host-side launch rules of csrc/common.h, checked without a GPU (built
-with g++ against the HIP headers), and the spread slice counters of the
+"""The host-side launch rules of csrc/common.h and csrc/gemv_tiles.h, checked
+without a GPU (built with g++ against the HIP headers), and the spread slice counters of the
 plan-free forward where they just fit its scratch array and where they do not."""
 import os
 import shutil
@@ -13,11 +13,12 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
                     reason="needs g++ and the HIP headers")
-def test_launch_rules(tmp_path):
-    exe = tmp_path / "launch_rules_check"
+@pytest.mark.parametrize("check", ["launch_rules_check", "gemv_tiles_check"])
+def test_launch_rules(check, tmp_path):
+    exe = tmp_path / check
     subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     "-I" + os.path.join(ROOT, "paper_2305_06942_amd", "csrc"), "-I" + os.path.join(ROOT, "include"),
-                    os.path.join(ROOT, "tests", "launch_rules_check.cpp"), "-o", str(exe)], check=True)
+                    os.path.join(ROOT, "tests", check + ".cpp"), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "bad=0" in r.stdout

@@ -730,10 +730,7 @@ int gemv_ar_unfused_forward(gemv_ar_t h, const void* const* A, const void* const
   if (rc) return rc;
   const int64_t g1 = (int64_t)h->R * h->n_tiles;
   if (g1 > INT_MAX) return fail(EBAG_EINVAL, "too many tiles for one launch");
-  if (g1 * h->split <= INT_MAX) {
-    a.split = h->split;
-    a.sub_rows = h->sub_rows;
-  }
+  a.split = split_for(g1, h->opts.waves_per_wg, a.TM, h->max_x_bytes, &a.sub_rows);
   hipLaunchKernelGGL(pick(h->dtype, GEMV_PARTIAL, h->rpi, h->xreg), dim3((unsigned)(g1 * a.split)), dim3(h->block),
                      h->lds_bytes(), stream, a);
   hipError_t e = hipGetLastError();

@@ -1,5 +1,6 @@
 // Host check of gemv_tiles.h: the workgroups of every owner visit each of its
-// tiles once and stop, up to 2^31 - 1 tiles.
+// tiles once and stop, up to 2^31 - 1 tiles; a split covers every row and leaves a
+// launch that fills the device as it is.
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -45,6 +46,16 @@ int main() {
             if (steps >= 10 || want < (int64_t)o.own[q + 1]) ++bad;
           }
       }
+  for (int64_t wgs : {(int64_t)1, (int64_t)8, (int64_t)51, (int64_t)1024, (int64_t)2048, (int64_t)16777216, most})
+    for (int W : {1, 2, 4, 16})
+      for (int TM : {1, 63, 64, 128, 4096})
+        for (int64_t bytes : {(int64_t)16, (int64_t)1024, (int64_t)65536}) {
+          ++cases;
+          int32_t sub = 0;
+          const int32_t split = split_for(wgs, W, TM, bytes, &sub);
+          if (split < 1 || sub < 1 || (int64_t)split * sub < TM || (int64_t)(split - 1) * sub >= TM) ++bad;
+          if (split > 1 && wgs * W * split > 2 * kTargetWaves) ++bad;
+        }
   std::printf("cases=%d bad=%d\n", cases, bad);
   return bad != 0;
 }

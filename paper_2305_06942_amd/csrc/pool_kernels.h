@@ -301,6 +301,7 @@ struct AnyTable {
   const char* colp;   // this lane's vector of row 0
   uint32_t rows, rb;
   int vb, G, g, v;    // g: beyond any bag in the lanes left over
+  int few_rows;
   bool tile;          // rows of at most 64 vectors leave through the LDS tile
   float* lrow;
   int dim;
@@ -314,6 +315,7 @@ struct AnyTable {
     dim = m.dim;
     first = block;
     vb = min(64, m.vecs - block);
+    few_rows = m.vshift < 0 ? 7 : 0;
     G = (int)(64u / (unsigned)vb);
     g = (int)((unsigned)lane / (unsigned)vb);
     v = lane - g * vb;
@@ -321,14 +323,16 @@ struct AnyTable {
     colp = static_cast<const char*>(tab) + (int64_t)(block + v) * 16;
   }
   __device__ __forceinline__ int groups() const { return G; }
-  // Weighted bags of fewer lookups are added row after row: every product is
-  // rounded by itself when rows go side by side, once with its sum when they
-  // follow each other, so side by side is the less accurate order below seven
-  // rows (rounding variances, in units of one product's, 2 rows: 4 against 3; 6:
-  // 22 and 21; 7: 24 and 28).  Bags of 1 to 3 lookups: 3.3e-8 off the sum in 64
+  // Weighted bags of fewer lookups are added row after row in every column block
+  // of a row that is no power of two of vectors: every product is rounded by
+  // itself when rows go side by side, once with its sum when they follow each
+  // other.  In units of one product's rounding variance, side by side over six
+  // groups or more against in sequence: 4 and 3 for 2 rows, 22 and 21 for 6, 27 and
+  // 28 for 7.  With fewer groups it is level sooner (2 groups at 4 rows, 3 at
+  // 5); 7 holds for every width.  Bags of 1 to 3 lookups: 3.3e-8 off the sum in 64
   // bits in sequence, 3.9e-8 side by side.  Rows of 2^k vectors go side by side
   // whatever the kernel.
-  __device__ __forceinline__ int few() const { return (vb & (vb - 1)) ? 7 : 0; }
+  __device__ __forceinline__ int few() const { return few_rows; }
   __device__ __forceinline__ int slot_lane() const { return g < G ? g : 0; }
   __device__ __forceinline__ u4v load(int32_t r, int left, bool* bad) const {
     const bool in = (uint32_t)r < rows;

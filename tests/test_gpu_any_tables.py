@@ -149,24 +149,29 @@ def test_rows_left_out_whatever_their_weight(vec, dtype):
     plan.close()
 
 
-@pytest.mark.parametrize("vec", [3, 6, 12, 20, 24])
-def test_short_weighted_bags_add_in_sequence(vec):
+@pytest.mark.parametrize("dtype", [synth.F32, synth.F16, synth.BF16])
+@pytest.mark.parametrize("vec", [3, 6, 12, 20, 24, 65, 72, 80, 96])
+def test_short_weighted_bags_add_in_sequence(vec, dtype):
     """Weighted bags of fewer than seven lookups of a table whose rows are no
-    power of two of vectors: fma(w, x, sum) row after row, bit for bit.  In 64
-    bits a product and its sum with the one before are exact here: weights are
-    multiples of 2^-24, fp16 values of 2^-24, sums stay below 2^5."""
+    power of two of vectors: fma(w, x, sum) row after row, bit for bit, in every
+    column block of a row.  In 64 bits a product and its sum with the one before
+    are exact here: weights are multiples of 2^-24, values of 2^-4 (below 8, so
+    exact in every storage type), sums stay below 2^6."""
     import torch
     B, rows = 56, 50
     L = np.tile(np.arange(8), 7)
-    inp = _inputs(synth.F16, [vec], L, rows, B, 1, 28, True, vec)
-    say("short weighted bags", vec)
+    inp = _inputs(dtype, [vec], L, rows, B, 1, 28, True, vec)
+    tab = np.clip(np.round(np.random.default_rng([2305, 6942, 70, vec]).standard_normal((rows, inp.w.dims[0])) * 16),
+                  -127, 127) / 16
+    inp.host_tables[0] = (tab.astype(np.float16) if dtype == synth.F16 else tab.astype(np.float32)
+                          if dtype == synth.F32 else synth.gen.f32_to_bf16_bits(tab.astype(np.float32)))
+    say("short weighted bags", vec, dtype)
     dev = sdev.to_device(inp)
     plan = make_plan(inp.w)
     send, _, flags = new_buffers(inp.w)
     run(plan, inp.w, dev, send, flags)
     torch.cuda.synchronize()
     got = send.cpu().numpy()
-    tab = inp.host_tables[0].astype(np.float64)
     for b in range(B):
         if L[b] > 6:
             continue

@@ -118,7 +118,10 @@ typedef struct ebag_a2a_opts {
   int32_t debug_suppress_flag; /* >= 0: never publish the flag with this index (failure-path tests); -1 off */
   int32_t consumer_wgs;        /* single-wave workgroups of the consumer kernel (default 512) */
   int32_t stream_rows;         /* 1 (default): table rows are read with non-temporal loads (no reuse expected);
-                                  0: cached loads (skewed index distributions with hot rows) */
+                                  0: cached loads (skewed index distributions with hot rows).  A plan with
+                                  check_indices, a table of 4 GiB or more or rows that are not 2^k <= 64
+                                  sixteen-byte vectors reads them cached unless every table's rows are
+                                  whole 128-byte lines */
   int64_t consume_timeout_us;  /* the consumer, and the backward waiting on gradient flags, give up after
                                   this long and report it through ebag_a2a_status (default 5,000,000 us) */
   int32_t pooling_mode;        /* 0 (default): sum (weighted sum when weights are given); 1: mean -- the

@@ -326,21 +326,6 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->per_table = o.slice_granule == 1;
 }
 
-PoolVariant ebag::pool_variant(const PoolSetup& s, bool fused, bool weighted) {
-  PoolVariant k;
-  k.dtype = s.dtype;
-  k.rows_in_flight = s.o->rows_in_flight;
-  k.weighted = weighted;
-  k.fused = fused;
-  k.stream_rows = s.o->stream_rows != 0;
-  k.any = s.o->check_indices != 0;
-  for (int32_t t = 0; t < s.T; ++t) {
-    const TabMeta& m = s.meta[t];
-    if (m.vshift < 0 || m.rows * m.row_bytes > (int64_t)0xFFFFFFFFll) k.any = true;
-  }
-  return k;
-}
-
 int ebag::pool_grid(const PoolSetup& s, int64_t nruns, const PoolVariant& k, int block, int out_floats) {
   int64_t grid = nruns;
   if (s.o->persistent_wgs_per_cu != 0) {

@@ -1,7 +1,8 @@
 // Host check of the launch rules in common.h that size and index device
 // memory: spread slice counters stay inside their allocation; division by a
 // launch constant is exact; the kernels' run decoding (run_at on a RunOrder)
-// is the one on the SliceOrder.
+// is the one on the SliceOrder; which pooling kernel and which loads a plan's
+// tables get.
 #include <cstdint>
 #include <cstdio>
 
@@ -52,6 +53,30 @@ int main() {
             if (gs2 != gs || (int32_t)tp2 != tp || (int32_t)j2 != j) ++bad;
           }
         }
+  struct Want { int64_t rows; int64_t bytes; int check; bool any, streams; };
+  for (const Want& w : {Want{1000, 512, 0, false, true}, Want{1000, 16, 0, false, true}, Want{1000, 512, 1, true, true},
+                        Want{1000, 64, 1, true, false}, Want{1000, 640, 0, true, true}, Want{1000, 192, 0, true, false},
+                        Want{1000, 2080, 0, true, false}, Want{1000, 1280, 0, true, true},
+                        Want{10000000, 512, 0, true, true}, Want{300000000, 16, 0, true, false}}) {
+    ebag_a2a_opts_t o{};
+    o.check_indices = w.check;
+    o.rows_in_flight = 8;
+    TabMeta m[2] = {};
+    m[0].rows = 10, m[0].row_bytes = 128, m[0].vecs = 8, m[0].vshift = 3;
+    m[1].rows = w.rows, m[1].row_bytes = w.bytes, m[1].vecs = (int32_t)(w.bytes / 16), m[1].vshift = -1;
+    for (int s = 0; s <= 6; ++s)
+      if (m[1].vecs == 1 << s) m[1].vshift = s;
+    PoolSetup ps{};
+    ps.o = &o;
+    ps.meta = m;
+    ps.T = 2;
+    for (int streams : {0, 1}) {
+      ++cases;
+      o.stream_rows = streams;
+      const PoolVariant k = pool_variant(ps, true, false);
+      if (k.any != w.any || k.stream_rows != (streams && w.streams)) ++bad;
+    }
+  }
   std::printf("cases=%d bad=%d\n", cases, bad);
   return bad != 0;
 }

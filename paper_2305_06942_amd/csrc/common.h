@@ -248,7 +248,24 @@ constexpr int32_t kStatusInit[4] = {0, 0x7fffffff, 0, 0x7fffffff};
 int fail(int code, const char* fmt, ...);
 void clear_error();
 
-constexpr int kPoolSlotWords = 576;  // LDS words of a pooling wave's index staging slot
+// Lookups a pooling wave stages in LDS at once.  With weights the general
+// kernel takes fewer, so that four waves' slots and a run's tile of 16 KiB fit
+// five times into a CU's 160 KiB, as its registers do: 8 fp16 tables of 1008-byte
+// rows that fit the caches, weighted bags of 1 to 100: 231 us with four workgroups
+// a CU, 190 us with five.
+constexpr int pool_staged(bool any, bool weighted) { return any && weighted ? 448 : 512; }
+// Words behind the last slot: a row group may read up to 63 entries past the
+// last index (what it reads there is not used), in the other slots the next
+// wave's.  A tail in each slot left no room for a second workgroup of 16 waves
+// with weights and a tile of 8 KiB: 77 us against 49 us, 8 fp32 tables of 512-byte
+// rows, bags of 0 to 3.
+constexpr int kPoolSlotTail = 64;
+
+// LDS of a pooling workgroup: the run-arrival counter and the ticket's
+// broadcast slot (16 bytes), a staging slot per wave, the tail, the run's tile.
+constexpr size_t pool_lds_bytes(bool any, bool weighted, int waves, int out_floats) {
+  return 16 + (size_t)waves * pool_staged(any, weighted) * (weighted ? 8 : 4) + (size_t)(kPoolSlotTail + out_floats) * 4;
+}
 
 hipError_t launch_pool(const PoolVariant& k, const PoolArgs& a, int grid, int block, hipStream_t stream);
 int pool_max_wgs_per_cu(const PoolVariant& k, int block, int out_floats);

@@ -12,10 +12,8 @@ pool_fn pick(const PoolVariant& k) {
   }
 }
 
-// The run-arrival counter and the ticket's broadcast slot (16 bytes), the
-// waves' staging slots, the run's tile.
 size_t lds_bytes(const PoolVariant& k, int block, int out_floats) {
-  return 16 + (size_t)(block / 64) * kPoolSlotWords * (k.weighted ? 8 : 4) + (size_t)out_floats * 4;
+  return pool_lds_bytes(k.any, k.weighted, block / 64, out_floats);
 }
 
 }  // namespace

@@ -50,10 +50,6 @@
 namespace ebag {
 namespace {
 
-constexpr int SEGW = 512;         // indices a wave stages at once for a block of bags
-// A wave's LDS slot: a row group may read up to 63 entries past the last index.
-static_assert(kPoolSlotWords >= SEGW + 64, "staging slot");
-
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 struct EF32 { static constexpr int EPV = 4; };
@@ -196,11 +192,11 @@ __device__ __forceinline__ void reduce_groups(float* acc, int vs) {
     acc[e] += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(acc[e]), 0x121, 0xf, 0xf, true));  // row_ror:1
 }
 
-// Stage indices (and weights, kPoolSlotWords words behind them) [base, base + n) into
-// this wave's LDS slot, n <= SEGW, 64 at a time through buffer descriptors: the
+// Stage indices (and weights, S words behind them) [base, base + n) into this
+// wave's LDS slot, n <= S, 64 at a time through buffer descriptors: the
 // tail's range check costs no instruction, so a block of a few lookups is one
 // load and one LDS write.
-template <bool WT>
+template <bool WT, int S>
 __device__ __forceinline__ void stage_block(const int32_t* idx, const float* wts, int64_t base, int n, int lane,
                                             int32_t* slot) {
   const __amdgpu_buffer_rsrc_t ri =
@@ -219,7 +215,7 @@ __device__ __forceinline__ void stage_block(const int32_t* idx, const float* wts
     for (int u = 0; u < 4; ++u) {
       if (u > 0 && i0 + 64 * u >= n) continue;
       slot[i0 + 64 * u + lane] = (int32_t)x[u];
-      if (WT) slot[kPoolSlotWords + i0 + 64 * u + lane] = (int32_t)y[u];
+      if (WT) slot[S + i0 + 64 * u + lane] = (int32_t)y[u];
     }
   }
 }
@@ -401,7 +397,7 @@ struct AnyTable {
 // bag, which goes on.  A bag with an index out of range reports itself: bad
 // carries over the pieces of one bag, report is the first bag's number (or
 // nullptr status).
-template <class E, int U, bool WT, class Table>
+template <class E, int U, bool WT, int S, class Table>
 __device__ __forceinline__ void gather_bags(Table& tb, int c, uint32_t bags, const int32_t* slot, int lane,
                                             bool closes, float* acc, int32_t* status, int64_t report, bool* carry) {
   constexpr int EPV = E::EPV;
@@ -426,7 +422,7 @@ __device__ __forceinline__ void gather_bags(Table& tb, int c, uint32_t bags, con
     for (int u = 0; u < U; ++u) {
       cnt[u] = few ? min(n, step) : n;
       r[u] = lg[pos];
-      wv[u] = WT ? (g < cnt[u] ? __int_as_float(lg[kPoolSlotWords + pos]) : 0.f) : one;
+      wv[u] = WT ? (g < cnt[u] ? __int_as_float(lg[S + pos]) : 0.f) : one;
       pos += step;
       n -= step;
       if (n <= 0) {
@@ -562,7 +558,7 @@ __device__ __forceinline__ void leave_runs(uint32_t* ticket) {
 // or, with per-table slices, the (slice, table) pair's (target C bags).  Wave
 // w pools a contiguous block of the run's bags: it reads the block's CSR
 // offsets (one lane each), stages the block's whole index segment into its
-// LDS slot when it fits (else bag by bag, SEGW at a time), then gathers every
+// LDS slot when it fits (else bag by bag, S at a time), then gathers every
 // bag into the run's LDS tile.  Rows of more than 64 vectors are pooled 64
 // vectors at a time and stored directly.
 template <class E, int U, bool WT, bool NT, bool FUSED, bool ANY>
@@ -578,8 +574,9 @@ __device__ __forceinline__ void pool_body() {
   // dim floats), with mean pooling their K bag lengths.
   int32_t* s_arrive = s_dyn;
   uint32_t* s_tick = reinterpret_cast<uint32_t*>(s_dyn + 1);
-  int32_t* slot = s_dyn + 4 + wid * kPoolSlotWords * (WT ? 2 : 1);
-  float* lds_out = reinterpret_cast<float*>(s_dyn + 4 + W * kPoolSlotWords * (WT ? 2 : 1));
+  constexpr int S = pool_staged(ANY, WT), slot_words = S * (WT ? 2 : 1);
+  int32_t* slot = s_dyn + 4 + wid * slot_words;
+  float* lds_out = reinterpret_cast<float*>(s_dyn + 4 + W * slot_words + kPoolSlotTail);
   if (threadIdx.x == 0) *s_arrive = 0;
   __syncthreads();
   // One-shot grid: workgroup i pools run i.  Persistent grid (fewer
@@ -621,7 +618,7 @@ __device__ __forceinline__ void pool_body() {
         const int64_t off = offs[blk + min(lane, c)];
         const int64_t seg_lo = min(max(sload(offs, blk), (int64_t)0), nnz);
         const int64_t seg_hi = min(max(sload(offs, blk + c), seg_lo), nnz);
-        bool all = seg_hi - seg_lo <= SEGW;  // the block's lookups fit the staging slot
+        bool all = seg_hi - seg_lo <= S;  // the block's lookups fit the staging slot
         uint64_t invalid = 0;
         if (Table::CHECKS && a.check) {
           const int64_t next = __shfl_down(off, 1);
@@ -630,7 +627,7 @@ __device__ __forceinline__ void pool_body() {
           if (lane < c && !ok) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(bag0 + blk + lane));
           if (invalid) all = false;
         }
-        if (all) stage_block<WT>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
+        if (all) stage_block<WT, S>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
         const int64_t rel = min(max(off, seg_lo), seg_hi) - seg_lo;
         const int64_t len = max((int64_t)__shfl_down(rel, 1) - rel, (int64_t)0);
         if (a.mean && lane < c) lens[blk + lane] = (float)(int)len;
@@ -653,7 +650,7 @@ __device__ __forceinline__ void pool_body() {
           for (int i = 0; i < c;) {
             bool closes = true;
             uint32_t bags = packed;
-            if (!all) {  // bag by bag, SEGW lookups at a time
+            if (!all) {  // bag by bag, S lookups at a time
               if (lo == hi) {
                 lo = sload(offs, blk + i);
                 hi = sload(offs, blk + i + 1);
@@ -665,14 +662,14 @@ __device__ __forceinline__ void pool_body() {
                 }
                 if (ANY && a.mean && lane == 0) lens[blk + i] = (float)(int)(hi - lo);
               }
-              const int n = (int)min((int64_t)SEGW, hi - lo);
-              stage_block<WT>(a.indices, a.weights, lo, n, lane, slot);
+              const int n = (int)min((int64_t)S, hi - lo);
+              stage_block<WT, S>(a.indices, a.weights, lo, n, lane, slot);
               bags = lane == 0 ? n : 0;
               lo += n;
               closes = lo == hi;
             }
             wave_lds_sync();
-            gather_bags<E, U, WT>(tb, all ? c : 1, bags, slot, lane, closes, acc, Table::CHECKS && a.check ? a.status : nullptr,
+            gather_bags<E, U, WT, S>(tb, all ? c : 1, bags, slot, lane, closes, acc, Table::CHECKS && a.check ? a.status : nullptr,
                                   bag0 + blk + i, &carry);
             wave_lds_sync();
             if (closes) i += all ? c : 1;

@@ -2,7 +2,8 @@
 // memory: spread slice counters stay inside their allocation; division by a
 // launch constant is exact; the kernels' run decoding (run_at on a RunOrder)
 // is the one on the SliceOrder; which pooling kernel and which loads a plan's
-// tables get.
+// tables get; pooling workgroups' LDS leaves a CU the workgroups that their
+// registers allow.
 #include <cstdint>
 #include <cstdio>
 
@@ -76,6 +77,14 @@ int main() {
       const PoolVariant k = pool_variant(ps, true, false);
       if (k.any != w.any || k.stream_rows != (streams && w.streams)) ++bad;
     }
+  }
+  // workgroups that fit a CU's 160 KiB: (any, weighted, waves, tile floats) -> at least
+  struct Fit { bool any, weighted; int waves, floats, at_least; };
+  for (const Fit& f : {Fit{false, true, 16, 2048, 2}, Fit{false, true, 8, 1024, 4}, Fit{false, true, 4, 4096, 4},
+                       Fit{false, false, 4, 4096, 6}, Fit{false, false, 16, 4096, 2}, Fit{true, true, 4, 4096, 5},
+                       Fit{true, false, 4, 4096, 6}, Fit{true, true, 16, 4096 + 1024, 1}}) {
+    ++cases;
+    if ((int64_t)pool_lds_bytes(f.any, f.weighted, f.waves, f.floats) * f.at_least > 160 * 1024) ++bad;
   }
   std::printf("cases=%d bad=%d\n", cases, bad);
   return bad != 0;

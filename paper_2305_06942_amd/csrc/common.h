@@ -148,8 +148,7 @@ struct PoolArgs {
   int32_t check;              // check offsets / indices
   int32_t release_mode;       // 0 agent-scope release fence, 1 device-scope stores + completion wait
   int32_t waves;              // wavefronts per workgroup (blockDim.x / 64)
-  int32_t out_floats;         // LDS output buffer of the fast path: K x max dim (mean: and K lengths)
-  int32_t stream_rows;        // 1: table rows loaded non-temporally
+  int32_t out_floats;         // LDS tile of the run's pooled rows: K x the widest of <= 64 vectors (mean: and K lengths)
   int32_t mean;               // 1: mean pooling (sum / bag length)
   int32_t per_table;          // 1: one flag / counter per (slice, table), index g * T + t
   int32_t counter_shift;
@@ -176,15 +175,19 @@ struct PoolSetup {
   uint32_t* d_ticket;
 };
 
-// Which of the pooling kernels a launch takes.  any: the one for any tables and
-// for index reports; else every table is below 4 GiB (32-bit offsets) with rows
-// of 2^k <= 64 sixteen-byte vectors, whose kernel needs far fewer registers
-// (fp16: 65 instead of 85) and reads such tables faster (26 tables x 16384 bags
-// of 0 to 3 rows of 512 bytes: 113 us, against 158 us by the other one).
+// Which of the pooling kernels a launch takes.  POOL_FAST: every table below 4
+// GiB (32-bit offsets) with rows of 2^k <= 64 sixteen-byte vectors, no index
+// report; its kernel needs fewer registers (fp32: 59 instead of 69 and 82) and
+// reads such tables faster (26 tables x 16384 bags of 0 to 3 rows of 512 bytes: 113
+// us, against 158 us by the general one).  POOL_NARROW, POOL_WIDE: the general
+// kernel for any tables and for index reports, without and with rows of more than
+// 32 vectors, whose code costs the others registers.
+enum PoolKind { POOL_FAST = 0, POOL_NARROW = 1, POOL_WIDE = 2 };
 struct PoolVariant {
   int dtype;
   int rows_in_flight;
-  bool weighted, fused, stream_rows, any;
+  bool weighted, fused, stream_rows;
+  PoolKind kind;
 };
 typedef void (*pool_fn)(const PoolArgs);
 pool_fn pick_pool_f32(const PoolVariant& k);
@@ -204,15 +207,28 @@ inline PoolVariant pool_variant(const PoolSetup& s, bool fused, bool weighted) {
   k.rows_in_flight = s.o->rows_in_flight;
   k.weighted = weighted;
   k.fused = fused;
-  k.any = s.o->check_indices != 0;
-  bool whole_lines = true;
+  bool any = s.o->check_indices != 0, wide = false, whole_lines = true;
   for (int32_t t = 0; t < s.T; ++t) {
     const TabMeta& m = s.meta[t];
-    if (m.vshift < 0 || m.rows * m.row_bytes > (int64_t)0xFFFFFFFFll) k.any = true;
+    if (m.vshift < 0 || m.rows * m.row_bytes > (int64_t)0xFFFFFFFFll) any = true;
+    if (m.vecs > 32) wide = true;
     if (m.row_bytes % 128) whole_lines = false;
   }
-  k.stream_rows = s.o->stream_rows && (!k.any || whole_lines);
+  k.kind = !any ? POOL_FAST : wide ? POOL_WIDE : POOL_NARROW;
+  k.stream_rows = s.o->stream_rows && (!any || whole_lines);
   return k;
+}
+
+// Most bags of a run whose pooled rows fit its LDS tile: 16 KiB, and in the
+// general kernels 4.5 KiB a wave, so that with its staging slot a wave stays below
+// the 8 KiB that the 20 waves their registers allow leave it.
+inline int32_t pool_tile_bags(PoolKind kind, int32_t waves, int32_t max_dim, int32_t tile_dim) {
+  int32_t bags = 16384 / (4 * max_dim);
+  if (kind != POOL_FAST && tile_dim > 0) {
+    const int32_t fit = (4608 * waves - 272) / (4 * tile_dim);
+    if (fit < bags) bags = fit;
+  }
+  return bags < 1 ? 1 : bags;
 }
 
 // Host helpers shared by the plan and the plan-free forward (plan.hip).

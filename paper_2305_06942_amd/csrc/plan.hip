@@ -283,12 +283,15 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   std::memset(a, 0, sizeof *a);
   const ebag_a2a_opts_t& o = *s.o;
   int32_t K = o.bags_per_run < s.C ? o.bags_per_run : s.C;
-  // The fast kernels keep a run's pooled rows in LDS (K x max dim floats):
-  // cap that buffer at 16 KiB.
-  int32_t max_dim = 0;
-  for (int32_t t = 0; t < s.T; ++t) max_dim = s.meta[t].dim > max_dim ? s.meta[t].dim : max_dim;
-  const int32_t k_cap = 16384 / (4 * max_dim) > 1 ? 16384 / (4 * max_dim) : 1;
-  if (K > k_cap) K = k_cap;
+  // Rows of more than 64 vectors do not go through the tile.
+  int32_t max_dim = 0, tile_dim = 0;
+  for (int32_t t = 0; t < s.T; ++t) {
+    const TabMeta& m = s.meta[t];
+    if (m.dim > max_dim) max_dim = m.dim;
+    if (m.vecs <= 64 && m.dim > tile_dim) tile_dim = m.dim;
+  }
+  const int32_t fit = pool_tile_bags(pool_variant(s, true, false).kind, o.waves_per_wg, max_dim, tile_dim);
+  if (K > fit) K = fit;
   a->tables = s.d_tables;
   a->meta = s.d_meta;
   a->tperm = s.d_tperm;
@@ -316,12 +319,7 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->check = o.check_indices;
   a->release_mode = o.release_mode;
   a->waves = o.waves_per_wg;
-  // Rows of more than 64 vectors do not go through the tile.
-  int32_t tile_dim = 0;
-  for (int32_t t = 0; t < s.T; ++t)
-    if (s.meta[t].vecs <= 64 && s.meta[t].dim > tile_dim) tile_dim = s.meta[t].dim;
   a->out_floats = K * tile_dim + (o.pooling_mode == 1 ? (K + 3) & ~3 : 0);
-  a->stream_rows = o.stream_rows;
   a->mean = o.pooling_mode == 1;
   a->per_table = o.slice_granule == 1;
 }

@@ -13,7 +13,7 @@ pool_fn pick(const PoolVariant& k) {
 }
 
 size_t lds_bytes(const PoolVariant& k, int block, int out_floats) {
-  return pool_lds_bytes(k.any, k.weighted, block / 64, out_floats);
+  return pool_lds_bytes(k.kind != POOL_FAST, k.weighted, block / 64, out_floats);
 }
 
 }  // namespace

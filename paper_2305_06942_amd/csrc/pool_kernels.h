@@ -2,10 +2,10 @@
 // each type's kernels are instantiated in a source file of their own
 // (pool_f32.hip, pool_f16.hip, pool_bf16.hip), which compile side by side.
 //
-// One wavefront pools one bag at a time (the paper's "logical workgroup" of
-// the EmbeddingBag kernel, Sec. III-A).  A workgroup takes a *run* of up to K
-// consecutive samples of one table inside one slice and its waves share the
-// run's bags; after the run the workgroup bumps that slice's counter once,
+// One wavefront pools whole bags (the paper's "logical workgroup" of the
+// EmbeddingBag kernel, Sec. III-A), a contiguous block of them.  A workgroup
+// takes a *run* of up to K consecutive samples of one table inside one slice and
+// its waves share the run's bags; after the run the workgroup bumps that slice's counter once,
 // and the arrival that completes the slice releases the slice's flag
 // (Sec. III-A, "Book-keeping Flags").
 //
@@ -23,16 +23,21 @@
 // destination slots with contiguous 16-byte stores, waits for them and updates
 // the slice counter -- no workgroup barrier, and no store queued ahead of a
 // gather load.  Tables below 4 GiB with V = 2^k and no index report take the
-// fast kernel (FastTable); any others the general one (AnyTable): G = 64/V
-// rounded down, V > 64 pooled 64 vectors at a time and stored directly.
+// fast kernel (FastTable).  Any others take the general one: V <= 32 G = 64/V
+// rounded down (AnyTable), wider rows 64 vectors at a time, a row a load
+// (WideTable), V > 64 stored directly; its waves store their own bags, from the
+// tile where V <= 64.
 // Long bags are bound by the memory system (512-byte rows arrive at the rate of
 // a random-row read probe); short ones by the waves in flight and by
 // instructions issued per bag, which is why the run's decoding divides by
 // multiplication, the kernel's arguments are re-read instead of kept
 // (late_args) and groups combine without LDS.  Measured at 26 tables x 16384
 // bags of 0 to 3 rows of 512 bytes (547 MB): 188 us with one bag at a time and
-// 81 vector registers (5 waves per SIMD), 112 us with 56 (8 waves), 4.9 TB/s;
-// 24 to 64 rows a bag are level (within 0.5% on the same buffers).
+// 81 vector registers (5 waves per SIMD), 112 us with 59 (8 waves), 4.9 TB/s;
+// 24 to 64 rows a bag are level (within 0.5% on the same buffers).  Vector
+// registers at U = 8, plain and weighted: fp32 59 and 68, fp16 65 and 72, bf16 64
+// and 71 (8 waves up to 64, 7 up to 72; above 96 scalar registers 7); general, narrow:
+// 69 and 77, 78 and 86, 77 and 82; wide: 82 and 89, 86 and 91, 85 and 91.
 //
 // Run order (run_at): by default runs are numbered slice-major (all runs of
 // slice 0, then slice 1 ...), tables fastest inside a slice, so slices
@@ -42,8 +47,6 @@
 // XCD's L2) or on the whole device (table_major = 2: the table shares the
 // Infinity Cache); with per-table slices those still complete progressively.
 #pragma once
-
-#include <type_traits>
 
 #include "common.h"
 
@@ -117,8 +120,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 typedef __attribute__((address_space(1))) const u4v gu4v;
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 
-// Output stores go through a buffer descriptor spanning exactly one pooled
-// row (out-of-range lanes are dropped by the hardware).  sc1 = 1 gives
+// Output stores go through a buffer descriptor spanning exactly the pooled rows
+// stored (out-of-range lanes are dropped by the hardware).  sc1 = 1 gives
 // device-scope stores: they complete at device scope, so a release needs no
 // L2 writeback for them; sc1 = 0 gives plain write-back stores.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(float* row, int bytes) {
@@ -231,12 +234,19 @@ __device__ __forceinline__ const PoolArgs& late_args() {
   return *(const PoolArgs*)p;
 }
 
-// A column block of Vb <= 64 sixteen-byte vectors of one table's rows, as the
-// lanes of a wave read it: lane (g, v) takes vector v of a row of group g, G =
-// 64 / Vb groups (rounded down; the lanes left over read nothing).  A pooled
-// row leaves through emit(): to the run's LDS tile (lrow: this lane's vector of
-// the next bag's row), or where a row has more than 64 vectors and takes
-// several blocks, straight to its destination.
+// This lane's part of a pooled row, into the run's LDS tile.
+template <int EPV>
+__device__ __forceinline__ void put_tile(float* lrow, const float* acc) {
+  float4* d = reinterpret_cast<float4*>(lrow);
+#pragma unroll
+  for (int h = 0; h < EPV / 4; ++h) d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+}
+
+// One table's rows as the lanes of a wave read them: lane (g, v) takes vector v
+// of a row of group g, G = 64 / V groups (rounded down; the lanes left over read
+// nothing).  A pooled row leaves through emit(): to the run's LDS tile (lrow:
+// this lane's vector of the next bag's row), or where a row has more than 64
+// vectors and takes several column blocks, straight to its destination.
 //
 // Fast tables (below 4 GiB, rows of 2^k <= 64 vectors, no index report): loads
 // go through a buffer descriptor covering exactly the table.  32-bit offsets
@@ -247,14 +257,14 @@ __device__ __forceinline__ const PoolArgs& late_args() {
 // being written) from L2 and the Infinity Cache.
 template <int EPV, bool NT>
 struct FastTable {
-  static constexpr bool CHECKS = false;
+  static constexpr bool CHECKS = false, WIDE = false;
   __amdgpu_buffer_rsrc_t rs;
   uint32_t col;  // byte offset of this lane's 16-byte vector inside a row
   int vs;        // log2 of the vectors per row
   int g;
   float* lrow;
   int dim;
-  __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int lane) {
+  __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int, int lane) {
     rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(tab), 0, (int)(uint32_t)(m.rows * m.row_bytes),
                                            kBufferWord3);
     vs = m.vshift;
@@ -263,6 +273,7 @@ struct FastTable {
     dim = m.dim;
   }
   __device__ __forceinline__ int groups() const { return 64 >> vs; }
+  __device__ __forceinline__ int vector(int lane) const { return lane & ((1 << vs) - 1); }
   __device__ __forceinline__ int few() const { return 0; }
   __device__ __forceinline__ int slot_lane() const { return g; }
   // Zeros, and no memory access, in lanes past the bag's end: their offset is
@@ -273,52 +284,75 @@ struct FastTable {
   }
   __device__ __forceinline__ void emit(float* acc) {
     reduce_groups<EPV>(acc, vs);
-    if (g == 0) {
-      float4* d = reinterpret_cast<float4*>(lrow);
-#pragma unroll
-      for (int h = 0; h < EPV / 4; ++h)
-        d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
-    }
+    if (g == 0) put_tile<EPV>(lrow, acc);
     lrow += dim;
   }
 };
 
-// Any table: any row width, 64-bit addresses, indices checked against the table
-// (a row out of range is skipped, and reported by the caller when the plan asks
-// for it).  Measured on 24 fp16 tables of 96 to 640-byte rows, bags of 1 to 40
-// (0.94 GB): 292 us with one row a load and one bag at a time, 236 us like this
-// -- its rows touch 8.7 M cache lines, which random reads return in about 175
-// us; reading tables below 4 GiB through a buffer descriptor here too left it
-// at 236 us.  Four fp32 tables of 5.1 GB, mean of 1 to 40 rows of 512 bytes
-// (0.72 GB): 156 us before, 141 us.
-template <int EPV, bool NT, bool FUSED>
+// Where the general kernel's pooled rows go that bypass the run's tile: straight
+// to their destination, a column block of vb vectors from `first` at a time.
+template <int EPV, bool FUSED>
+struct DirectRows {
+  int first, dim, t;  // first vector, floats of a row, table
+  int64_t bag;        // the next bag's sample
+  const float* len;   // and, mean pooling, its length
+  // acc: vector v of the row, in the lanes that hold one (on).
+  __device__ __forceinline__ void store(float* acc, int v, bool on) {
+    const PoolArgs& a = late_args();
+    if (a.mean) {
+      const float d = *len;
+#pragma unroll
+      for (int e = 0; e < EPV; ++e) acc[e] = d > 0.f ? acc[e] / d : acc[e];
+    }
+    const int col_off = sload(&a.meta[t].col_off, 0);
+    float* row = a.out + (FUSED ? bag * a.sum_dim + col_off : a.B * col_off + bag * dim);
+    if (on) {
+      const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, dim * 4);
+#pragma unroll
+      for (int h = 0; h < EPV / 4; ++h)
+        store16(rs, ((first + v) * EPV + 4 * h) * 4, acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3],
+                FUSED && a.release_mode == 1);
+    }
+    ++bag;
+    ++len;
+  }
+};
+
+// Rows of at most 32 vectors of any table, or (WITH_WIDE: not of a narrow plan)
+// the last column block, of at most 32 vectors, of wider ones: any width, 64-bit
+// addresses, indices checked against the table (a row out of range is skipped, and
+// reported by the caller when the plan asks for it).  Measured on 24 fp16 tables of
+// 96 to 640-byte rows, bags of 1 to 40 (0.94 GB): 292 us with one row a load and
+// one bag at a time, 236 us like this -- its rows touch 8.7 M cache lines, which
+// random reads return in about 175 us; reading tables below 4 GiB through a buffer
+// descriptor here too left it at 236 us.  Four fp32 tables of 5.1 GB, mean of 1 to
+// 40 rows of 512 bytes (0.72 GB): 156 us before, 141 us.
+template <int EPV, bool NT, bool FUSED, bool WITH_WIDE>
 struct AnyTable {
-  static constexpr bool CHECKS = true;
+  static constexpr bool CHECKS = true, WIDE = false;
   const char* colp;   // this lane's vector of row 0
   uint32_t rows, rb;
   int vb, G, g, v;    // g: beyond any bag in the lanes left over
   int few_rows;
-  bool tile;          // rows of at most 64 vectors leave through the LDS tile
+  bool tile;          // a whole row: leaves through the LDS tile
   float* lrow;
   int dim;
-  int first;          // direct: first vector of the block,
-  int t;              // the table,
-  int64_t bag;        // the next bag's sample
-  const float* len;   // and, mean pooling, its length
+  DirectRows<EPV, FUSED> direct;
   __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int block, int lane) {
     rows = (uint32_t)m.rows;
     rb = (uint32_t)m.row_bytes;
     dim = m.dim;
-    first = block;
-    vb = min(64, m.vecs - block);
-    few_rows = m.vshift < 0 ? 7 : 0;
+    vb = m.vecs - block;
     G = (int)(64u / (unsigned)vb);
     g = (int)((unsigned)lane / (unsigned)vb);
     v = lane - g * vb;
     if (g >= G) g = 1 << 20;
     colp = static_cast<const char*>(tab) + (int64_t)(block + v) * 16;
+    tile = block == 0;
+    few_rows = m.vshift < 0 ? 7 : 0;
   }
   __device__ __forceinline__ int groups() const { return G; }
+  __device__ __forceinline__ int vector(int) const { return v; }
   // Weighted bags of fewer lookups are added row after row in every column block
   // of a row that is no power of two of vectors: every product is rounded by
   // itself when rows go side by side, once with its sum when they follow each
@@ -350,35 +384,46 @@ struct AnyTable {
         acc[e] = take ? acc[e] + x : acc[e];
       }
     }
-    if (tile) {
-      if (g == 0) {
-        float4* d = reinterpret_cast<float4*>(lrow);
-#pragma unroll
-        for (int h = 0; h < EPV / 4; ++h)
-          d[h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
-      }
-      lrow += dim;
+    if (WITH_WIDE && !tile) {
+      direct.store(acc, v, g == 0);
       return;
     }
-    store_row(acc);
-    ++bag;
-    ++len;
+    if (g == 0) put_tile<EPV>(lrow, acc);
+    lrow += dim;
   }
-  __device__ __forceinline__ void store_row(float* acc) const {
-    const PoolArgs& a = late_args();
-    if (a.mean) {
-      const float d = *len;
-#pragma unroll
-      for (int e = 0; e < EPV; ++e) acc[e] = d > 0.f ? acc[e] / d : acc[e];
-    }
-    const int col_off = sload(&a.meta[t].col_off, 0);
-    float* row = a.out + (FUSED ? bag * a.sum_dim + col_off : a.B * col_off + bag * dim);
-    if (g == 0) {
-      const __amdgpu_buffer_rsrc_t rs = row_rsrc(row, dim * 4);
-#pragma unroll
-      for (int h = 0; h < EPV / 4; ++h)
-        store16(rs, ((first + v) * EPV + 4 * h) * 4, acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3],
-                FUSED && a.release_mode == 1);
+};
+
+// Rows of more than 32 vectors of any table, 64 at a time: a row (a column block
+// of it) takes the whole wave, so a load is one lookup (gather_rows).
+template <int EPV, bool NT, bool FUSED>
+struct WideTable {
+  static constexpr bool CHECKS = true, WIDE = true;
+  const char* colp;   // this lane's vector of row 0
+  uint32_t rows, rb;
+  int vb, v;
+  bool tile;          // a whole row: leaves through the LDS tile
+  float* lrow;
+  DirectRows<EPV, FUSED> direct;
+  __device__ __forceinline__ void init(const void* tab, const TabMeta& m, int block, int lane) {
+    rows = (uint32_t)m.rows;
+    rb = (uint32_t)m.row_bytes;
+    vb = min(64, m.vecs - block);
+    v = lane;
+    tile = m.vecs <= 64;
+    colp = static_cast<const char*>(tab) + (int64_t)(block + lane) * 16;
+  }
+  __device__ __forceinline__ int vector(int) const { return v; }
+  __device__ __forceinline__ bool active() const { return v < vb; }  // lanes that hold a vector
+  __device__ __forceinline__ u4v load(uint32_t r) const {
+    gu4v* p = (gu4v*)(colp + (uint64_t)r * rb);
+    return NT ? __builtin_nontemporal_load(p) : *p;
+  }
+  __device__ __forceinline__ void emit(float* acc) {
+    if (tile) {
+      put_tile<EPV>(lrow, acc);
+      lrow += direct.dim;
+    } else {
+      direct.store(acc, v, true);
     }
   }
 };
@@ -464,6 +509,75 @@ __device__ __forceinline__ void gather_bags(Table& tb, int c, uint32_t bags, con
   }
 }
 
+// gather_bags where a row takes the whole wave: a load is one staged lookup, so
+// a block's loads are its lookups in order, whatever bags they belong to, and
+// need none of the bookkeeping of groups.  A chunk of U lookups whose rows are all
+// in the table is checked once, by its largest index.  Rows that come from the
+// caches are bound by the instructions issued per row: 8 fp32 tables of 1008-byte
+// rows that fit them, weighted bags of 1 to 100, 209 us in gather_bags and 135 us
+// here (138 us one bag at a time without any check); that do not, 489 us and 494
+// us (514 us).
+template <class E, int U, bool WT, int S, class Table>
+__device__ __forceinline__ void gather_rows(Table& tb, int c, uint32_t bags, const int32_t* slot, int lane,
+                                            bool closes, float* acc, int32_t* status, int64_t report, bool* carry) {
+  const uint32_t ends = (bags >> 16) + (bags & 0xffff);
+  const int total = __builtin_amdgcn_readlane(ends, c - 1);
+  float one = 1.f;  // as in gather_bags
+  asm("" : "+v"(one));
+  int bag = closes ? 0 : c;
+  int end = __builtin_amdgcn_readlane(ends, 0);  // lookups up to the bag's last
+  // With k lookups added: the bags that end there.
+  const auto close = [&](int k) __attribute__((always_inline)) {
+    while (bag < c && end <= k) {
+      if (tb.active()) tb.emit(acc);
+#pragma unroll
+      for (int e = 0; e < E::EPV; ++e) acc[e] = 0.f;
+      if (*carry && lane == 0) atomicMin(&status[ST_FIRST_BAD_BAG], (int32_t)(report + bag));
+      *carry = false;
+      ++bag;
+      end = __builtin_amdgcn_readlane(ends, min(bag, 63));
+    }
+  };
+  close(0);
+  for (int k0 = 0; k0 < total; k0 += U) {
+    uint32_t r[U], most = 0;
+    float wv[U];
+    uint32_t bads = 0;
+#pragma unroll
+    for (int u = 0; u < U; u += 4) {
+      const u4v x = *reinterpret_cast<const u4v*>(slot + k0 + u);
+      r[u] = x.x, r[u + 1] = x.y, r[u + 2] = x.z, r[u + 3] = x.w;
+      const u4v y = WT ? *reinterpret_cast<const u4v*>(slot + S + k0 + u) : u4v{0u, 0u, 0u, 0u};
+      wv[u] = WT ? __uint_as_float(y.x) : one, wv[u + 1] = WT ? __uint_as_float(y.y) : one;
+      wv[u + 2] = WT ? __uint_as_float(y.z) : one, wv[u + 3] = WT ? __uint_as_float(y.w) : one;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) most = max(most, r[u]);
+    u4v raw[U];
+    if (k0 + U <= total && (uint32_t)__builtin_amdgcn_readfirstlane(most) < tb.rows) {
+      if (tb.active()) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = tb.load(r[u]);
+      }
+    } else {  // the block's end, or a row out of range, which is left out whatever its weight
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool on = k0 + u < total, in = on && r[u] < tb.rows;
+        raw[u] = u4v{0u, 0u, 0u, 0u};
+        if (in && tb.active()) raw[u] = tb.load(r[u]);
+        if (WT) wv[u] = in ? wv[u] : 0.f;
+        if (status) bads |= __any(on && !in) ? 1u << u : 0u;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      Widen<E>::template add<WT>(acc, raw[u], wv[u]);
+      *carry |= bads >> u & 1u;
+      close(k0 + u + 1);
+    }
+  }
+}
+
 // Write nb pooled rows of dim floats from LDS to global rows base + i * stride:
 // 64 lanes x 16 bytes per instruction, each row contiguous; a lane steps its
 // (row, vector) by 64 vectors; P2: dim is a power of two.  len:
@@ -500,9 +614,9 @@ __device__ __forceinline__ void store_rows(const float* lds, const float* len, i
 // Completion of one run (fused only).  release_mode 0: the workgroup's
 // stores are published by an agent-scope release on the slice counter (an L2
 // writeback on every run).  release_mode 1: the pooled vectors were stored
-// with device-scope stores, each wave waited for them to complete at device
-// scope (vmcnt 0) before the barrier, so the counter update needs no cache
-// writeback.  The arrival that completes the slice re-arms the counter and
+// with device-scope stores, and the waves that stored them waited for them to
+// complete at device scope (vmcnt 0) before this, so the counter update needs no
+// cache writeback.  The arrival that completes the slice re-arms the counter and
 // increments the slice flag.
 __device__ __forceinline__ void release_slice(uint32_t* counters, uint32_t* flags, int64_t g, uint32_t n,
                                               uint32_t target, int64_t suppress, uint64_t* trace, int mode,
@@ -553,18 +667,108 @@ __device__ __forceinline__ void leave_runs(uint32_t* ticket) {
   }
 }
 
+// A wave's bags [wid * per, ...) of a run, in blocks of at most 63: reads the
+// block's CSR offsets (one lane each), stages the block's whole index segment
+// into the wave's LDS slot when it fits (else bag by bag, S at a time), then
+// gathers vectors [first, last) of every bag.  Where one staged block was all of
+// the wave's bags, that is returned and *bags is what gather_bags takes for it; a
+// call for other vectors of the same bags is then passed both and reads nothing
+// again.
+template <class E, int U, bool WT, class Table>
+__device__ __forceinline__ bool pool_blocks(const PoolArgs& a, const TabMeta& m, const void* tab, int t, int64_t b0,
+                                            int nb, int per, int wid, int lane, int32_t* slot, float* lds_out,
+                                            int first, int last, bool staged, uint32_t* kept) {
+  constexpr int EPV = E::EPV;
+  constexpr int S = pool_staged(Table::CHECKS, WT);
+  const int64_t bag0 = (int64_t)t * a.B + b0;  // the run's first bag
+  const int64_t* offs = a.offsets + bag0;
+  float* lens = lds_out + a.out_floats - ((a.K + 3) & ~3);  // mean pooling
+  const int end = min((wid + 1) * per, nb);
+  float acc[EPV];
+#pragma unroll
+  for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
+  bool whole = false;
+  for (int blk = wid * per; blk < end; blk += 63) {
+    const int c = min(63, end - blk);
+    // Offsets are clamped into [0, nnz] and each bag into the block's
+    // segment, so malformed CSR input can never drive a read outside the
+    // index array (results are then meaningless but memory-safe).  With
+    // index checks a bag of invalid offsets is empty and reported, and its
+    // block goes bag by bag, which leaves the valid bags beside it whole.
+    int64_t seg_lo = 0, seg_hi = 0;
+    bool all = true;  // the block's lookups fit the staging slot
+    uint64_t invalid = 0;
+    uint32_t packed = *kept;
+    if (!staged) {
+      const int64_t off = offs[blk + min(lane, c)];
+      const int64_t nnz = sload(a.offsets, (int64_t)a.T * a.B);
+      seg_lo = min(max(sload(offs, blk), (int64_t)0), nnz);
+      seg_hi = min(max(sload(offs, blk + c), seg_lo), nnz);
+      all = seg_hi - seg_lo <= S;
+      if (Table::CHECKS && a.check) {
+        const int64_t next = __shfl_down(off, 1);
+        const bool ok = off >= 0 && off <= next && next <= nnz;
+        invalid = __ballot(lane < c && !ok);
+        if (lane < c && !ok) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(bag0 + blk + lane));
+        if (invalid) all = false;
+      }
+      if (all) stage_block<WT, S>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
+      const int64_t rel = min(max(off, seg_lo), seg_hi) - seg_lo;
+      const int64_t len = max((int64_t)__shfl_down(rel, 1) - rel, (int64_t)0);
+      if (a.mean && lane < c) lens[blk + lane] = (float)(int)len;
+      packed = all && lane < c ? (uint32_t)rel << 16 | (uint32_t)len : 0u;
+    }
+    for (int col = first; col < last; col += 64) {
+      Table tb;
+      tb.init(tab, m, col, lane);
+      tb.lrow = lds_out + blk * m.dim + tb.vector(lane) * EPV;
+      if constexpr (Table::CHECKS) tb.direct = {col, m.dim, t, b0 + blk, lens + blk};
+      bool carry = false;
+      int64_t lo = 0, hi = 0;
+      for (int i = 0; i < c;) {
+        bool closes = true;
+        uint32_t bags = packed;
+        if (!all) {  // bag by bag, S lookups at a time
+          if (lo == hi) {
+            lo = sload(offs, blk + i);
+            hi = sload(offs, blk + i + 1);
+            if (!Table::CHECKS || !a.check) {
+              lo = min(max(lo, seg_lo), seg_hi);
+              hi = min(max(hi, lo), seg_hi);
+            } else if (invalid >> i & 1u) {
+              lo = hi = 0;
+            }
+            if (Table::CHECKS && a.mean && lane == 0) lens[blk + i] = (float)(int)(hi - lo);
+          }
+          const int n = (int)min((int64_t)S, hi - lo);
+          stage_block<WT, S>(a.indices, a.weights, lo, n, lane, slot);
+          bags = lane == 0 ? n : 0;
+          lo += n;
+          closes = lo == hi;
+        }
+        int32_t* status = Table::CHECKS && a.check ? a.status : nullptr;
+        wave_lds_sync();
+        if constexpr (Table::WIDE)
+          gather_rows<E, U, WT, S>(tb, all ? c : 1, bags, slot, lane, closes, acc, status, bag0 + blk + i, &carry);
+        else
+          gather_bags<E, U, WT, S>(tb, all ? c : 1, bags, slot, lane, closes, acc, status, bag0 + blk + i, &carry);
+        wave_lds_sync();
+        if (closes) i += all ? c : 1;
+      }
+    }
+    whole = all && c == end - wid * per;
+    *kept = packed;
+  }
+  return whole;
+}
+
 // One workgroup per run of up to K consecutive samples of one table inside one
 // slice.  The counter it feeds is the slice's (target C * T bags)
 // or, with per-table slices, the (slice, table) pair's (target C bags).  Wave
-// w pools a contiguous block of the run's bags: it reads the block's CSR
-// offsets (one lane each), stages the block's whole index segment into its
-// LDS slot when it fits (else bag by bag, S at a time), then gathers every
-// bag into the run's LDS tile.  Rows of more than 64 vectors are pooled 64
-// vectors at a time and stored directly.
-template <class E, int U, bool WT, bool NT, bool FUSED, bool ANY>
+// w pools a contiguous block of the run's bags (pool_blocks).
+template <class E, int U, bool WT, bool NT, bool FUSED, int KIND>
 __device__ __forceinline__ void pool_body() {
   constexpr int EPV = E::EPV;
-  typedef std::conditional_t<ANY, AnyTable<EPV, NT, FUSED>, FastTable<EPV, NT>> Table;
   extern __shared__ int32_t s_dyn[];
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -574,7 +778,7 @@ __device__ __forceinline__ void pool_body() {
   // dim floats), with mean pooling their K bag lengths.
   int32_t* s_arrive = s_dyn;
   uint32_t* s_tick = reinterpret_cast<uint32_t*>(s_dyn + 1);
-  constexpr int S = pool_staged(ANY, WT), slot_words = S * (WT ? 2 : 1);
+  constexpr int slot_words = pool_staged(KIND != POOL_FAST, WT) * (WT ? 2 : 1);
   int32_t* slot = s_dyn + 4 + wid * slot_words;
   float* lds_out = reinterpret_cast<float*>(s_dyn + 4 + W * slot_words + kPoolSlotTail);
   if (threadIdx.x == 0) *s_arrive = 0;
@@ -600,87 +804,39 @@ __device__ __forceinline__ void pool_body() {
       const PoolArgs& a = late_args();
       const TabMeta m = load_meta(a.meta + t);
       const void* tab = sload(a.tables, t);
-      const int64_t nnz = sload(a.offsets, (int64_t)a.T * a.B);
-      const int64_t bag0 = (int64_t)t * a.B + b0;  // the run's first bag
-      const int64_t* offs = a.offsets + bag0;
-      float* lens = lds_out + a.out_floats - ((a.K + 3) & ~3);  // mean pooling
-      const int end = min((wid + 1) * per, nb);
-      float acc[EPV];
-#pragma unroll
-      for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-      for (int blk = wid * per; blk < end; blk += 63) {
-        const int c = min(63, end - blk);
-        // Offsets are clamped into [0, nnz] and each bag into the block's
-        // segment, so malformed CSR input can never drive a read outside the
-        // index array (results are then meaningless but memory-safe).  With
-        // index checks a bag of invalid offsets is empty and reported, and its
-        // block goes bag by bag, which leaves the valid bags beside it whole.
-        const int64_t off = offs[blk + min(lane, c)];
-        const int64_t seg_lo = min(max(sload(offs, blk), (int64_t)0), nnz);
-        const int64_t seg_hi = min(max(sload(offs, blk + c), seg_lo), nnz);
-        bool all = seg_hi - seg_lo <= S;  // the block's lookups fit the staging slot
-        uint64_t invalid = 0;
-        if (Table::CHECKS && a.check) {
-          const int64_t next = __shfl_down(off, 1);
-          const bool ok = off >= 0 && off <= next && next <= nnz;
-          invalid = __ballot(lane < c && !ok);
-          if (lane < c && !ok) atomicMin(&a.status[ST_FIRST_BAD_BAG], (int32_t)(bag0 + blk + lane));
-          if (invalid) all = false;
-        }
-        if (all) stage_block<WT, S>(a.indices, a.weights, seg_lo, (int)(seg_hi - seg_lo), lane, slot);
-        const int64_t rel = min(max(off, seg_lo), seg_hi) - seg_lo;
-        const int64_t len = max((int64_t)__shfl_down(rel, 1) - rel, (int64_t)0);
-        if (a.mean && lane < c) lens[blk + lane] = (float)(int)len;
-        const uint32_t packed = all && lane < c ? (uint32_t)rel << 16 | (uint32_t)len : 0u;
-        for (int col = 0; col < (ANY ? m.vecs : 1); col += 64) {
-          Table tb;
-          if constexpr (ANY) {
-            tb.init(tab, m, col, lane);
-            tb.tile = m.vecs <= 64;
-            tb.lrow = lds_out + blk * m.dim + tb.v * EPV;
-            tb.t = t;
-            tb.bag = b0 + blk;
-            tb.len = lens + blk;
-          } else {
-            tb.init(tab, m, lane);
-            tb.lrow = lds_out + blk * m.dim + (lane & ((1 << tb.vs) - 1)) * EPV;
-          }
-          bool carry = false;
-          int64_t lo = 0, hi = 0;
-          for (int i = 0; i < c;) {
-            bool closes = true;
-            uint32_t bags = packed;
-            if (!all) {  // bag by bag, S lookups at a time
-              if (lo == hi) {
-                lo = sload(offs, blk + i);
-                hi = sload(offs, blk + i + 1);
-                if (!Table::CHECKS || !a.check) {
-                  lo = min(max(lo, seg_lo), seg_hi);
-                  hi = min(max(hi, lo), seg_hi);
-                } else if (invalid >> i & 1u) {
-                  lo = hi = 0;
-                }
-                if (ANY && a.mean && lane == 0) lens[blk + i] = (float)(int)(hi - lo);
-              }
-              const int n = (int)min((int64_t)S, hi - lo);
-              stage_block<WT, S>(a.indices, a.weights, lo, n, lane, slot);
-              bags = lane == 0 ? n : 0;
-              lo += n;
-              closes = lo == hi;
-            }
-            wave_lds_sync();
-            gather_bags<E, U, WT, S>(tb, all ? c : 1, bags, slot, lane, closes, acc, Table::CHECKS && a.check ? a.status : nullptr,
-                                  bag0 + blk + i, &carry);
-            wave_lds_sync();
-            if (closes) i += all ? c : 1;
-          }
-        }
+      if constexpr (KIND == POOL_FAST) {
+        uint32_t kept = 0;
+        pool_blocks<E, U, WT, FastTable<EPV, NT>>(a, m, tab, t, b0, nb, per, wid, lane, slot, lds_out, 0, 1, false,
+                                                  &kept);
+      } else {
+        // the row's last column block of at most 32 vectors (the whole of a narrow row)
+        const int rest = KIND == POOL_NARROW ? m.vecs : (m.vecs & 63) <= 32 ? m.vecs & 63 : 0;
+        bool staged = false;
+        uint32_t kept = 0;
+        if constexpr (KIND == POOL_WIDE)
+          if (m.vecs > rest)
+            staged = pool_blocks<E, U, WT, WideTable<EPV, NT, FUSED>>(a, m, tab, t, b0, nb, per, wid, lane, slot, lds_out,
+                                                                      0, m.vecs - rest, false, &kept);
+        if (rest)
+          pool_blocks<E, U, WT, AnyTable<EPV, NT, FUSED, KIND == POOL_WIDE>>(a, m, tab, t, b0, nb, per, wid, lane, slot,
+                                                                             lds_out, m.vecs - rest, m.vecs, staged, &kept);
       }
     }
-    // Directly stored rows of this wave are complete before it arrives.
-    if (ANY) wait_stores_complete();
-    // The last wave to finish its bags writes the whole run from LDS to
-    // global memory and (fused) completes the run for the slice; the other
+    // General kernels: a wave stores its own rows, and they are complete before it
+    // arrives.
+    if constexpr (KIND != POOL_FAST) {
+      const PoolArgs& a = late_args();
+      const int dim = sload(&a.meta[t].dim, 0), col_off = sload(&a.meta[t].col_off, 0);
+      const int64_t stride = FUSED ? a.sum_dim : dim;
+      const int i0 = wid * per, n = min(per, nb - i0);
+      if (n > 0 && (KIND == POOL_NARROW || sload(&a.meta[t].vecs, 0) <= 64))
+        store_rows<false>(lds_out + i0 * dim, a.mean ? lds_out + a.out_floats - ((a.K + 3) & ~3) + i0 : nullptr, n,
+                          a.out + (FUSED ? col_off : a.B * col_off) + (b0 + i0) * stride, stride, dim, lane,
+                          FUSED && a.release_mode == 1);
+      wait_stores_complete();
+    }
+    // The last wave to finish its bags (fast kernel) writes the whole run from LDS
+    // to global memory and (fused) completes the run for the slice; the other
     // waves leave at once.  No workgroup barrier, and no store ever sits in
     // front of a gather load of the same wave.
     int old = 0;
@@ -689,13 +845,12 @@ __device__ __forceinline__ void pool_body() {
     if (old == W - 1) {
       const PoolArgs& a = late_args();
       if (lane == 0) __hip_atomic_store(s_arrive, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const int dim = sload(&a.meta[t].dim, 0), col_off = sload(&a.meta[t].col_off, 0);
-      const bool tile = !ANY || sload(&a.meta[t].vecs, 0) <= 64;
-      const int64_t stride = FUSED ? a.sum_dim : dim;
-      float* base = a.out + (FUSED ? col_off : a.B * col_off) + b0 * stride;
-      if (tile)
-        store_rows<!ANY>(lds_out, a.mean ? lds_out + a.out_floats - ((a.K + 3) & ~3) : nullptr, nb, base, stride, dim,
+      if constexpr (KIND == POOL_FAST) {
+        const int dim = sload(&a.meta[t].dim, 0), col_off = sload(&a.meta[t].col_off, 0);
+        const int64_t stride = FUSED ? a.sum_dim : dim;
+        store_rows<true>(lds_out, a.mean ? lds_out + a.out_floats - ((a.K + 3) & ~3) : nullptr, nb, a.out + (FUSED ? col_off : a.B * col_off) + b0 * stride, stride, dim,
                          lane, FUSED && a.release_mode == 1);
+      }
       if (FUSED) {
         if (a.release_mode == 1) wait_stores_complete();
         if (lane == 0)
@@ -710,30 +865,31 @@ __device__ __forceinline__ void pool_body() {
 
 // Fused operator: pooled vectors go straight to the send layout and slices
 // are released as they complete.
-template <class E, int U, bool WT, bool NT, bool ANY>
+template <class E, int U, bool WT, bool NT, int KIND>
 __global__ __launch_bounds__(1024) void fused_pool_kernel(const PoolArgs a) {
-  pool_body<E, U, WT, NT, true, ANY>();
+  pool_body<E, U, WT, NT, true, KIND>();
 }
 
 // Unfused baseline, first kernel: plain per-table EmbeddingBag output.
-template <class E, int U, bool WT, bool NT, bool ANY>
+template <class E, int U, bool WT, bool NT, int KIND>
 __global__ __launch_bounds__(1024) void unfused_pool_kernel(const PoolArgs a) {
-  pool_body<E, U, WT, NT, false, ANY>();
+  pool_body<E, U, WT, NT, false, KIND>();
 }
 
-template <class E, int U, bool WT, bool NT, bool ANY>
+template <class E, int U, bool WT, bool NT, int KIND>
 pool_fn pick_f(const PoolVariant& k) {
-  return k.fused ? &fused_pool_kernel<E, U, WT, NT, ANY> : &unfused_pool_kernel<E, U, WT, NT, ANY>;
+  return k.fused ? &fused_pool_kernel<E, U, WT, NT, KIND> : &unfused_pool_kernel<E, U, WT, NT, KIND>;
 }
 
-template <class E, int U, bool WT, bool ANY>
+template <class E, int U, bool WT, int KIND>
 pool_fn pick_n(const PoolVariant& k) {
-  return k.stream_rows ? pick_f<E, U, WT, true, ANY>(k) : pick_f<E, U, WT, false, ANY>(k);
+  return k.stream_rows ? pick_f<E, U, WT, true, KIND>(k) : pick_f<E, U, WT, false, KIND>(k);
 }
 
 template <class E, int U, bool WT>
 pool_fn pick_t(const PoolVariant& k) {
-  return k.any ? pick_n<E, U, WT, true>(k) : pick_n<E, U, WT, false>(k);
+  return k.kind == POOL_FAST ? pick_n<E, U, WT, POOL_FAST>(k)
+         : k.kind == POOL_NARROW ? pick_n<E, U, WT, POOL_NARROW>(k) : pick_n<E, U, WT, POOL_WIDE>(k);
 }
 
 template <class E>

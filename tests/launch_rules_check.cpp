@@ -54,11 +54,11 @@ int main() {
             if (gs2 != gs || (int32_t)tp2 != tp || (int32_t)j2 != j) ++bad;
           }
         }
-  struct Want { int64_t rows; int64_t bytes; int check; bool any, streams; };
-  for (const Want& w : {Want{1000, 512, 0, false, true}, Want{1000, 16, 0, false, true}, Want{1000, 512, 1, true, true},
-                        Want{1000, 64, 1, true, false}, Want{1000, 640, 0, true, true}, Want{1000, 192, 0, true, false},
-                        Want{1000, 2080, 0, true, false}, Want{1000, 1280, 0, true, true},
-                        Want{10000000, 512, 0, true, true}, Want{300000000, 16, 0, true, false}}) {
+  struct Want { int64_t rows; int64_t bytes; int check; PoolKind kind; bool streams; };
+  for (const Want& w : {Want{1000, 512, 0, POOL_FAST, true}, Want{1000, 16, 0, POOL_FAST, true}, Want{1000, 512, 1, POOL_NARROW, true},
+                        Want{1000, 64, 1, POOL_NARROW, false}, Want{1000, 640, 0, POOL_WIDE, true}, Want{1000, 192, 0, POOL_NARROW, false},
+                        Want{1000, 2080, 0, POOL_WIDE, false}, Want{1000, 1280, 0, POOL_WIDE, true},
+                        Want{10000000, 512, 0, POOL_NARROW, true}, Want{300000000, 16, 0, POOL_NARROW, false}}) {
     ebag_a2a_opts_t o{};
     o.check_indices = w.check;
     o.rows_in_flight = 8;
@@ -75,9 +75,20 @@ int main() {
       ++cases;
       o.stream_rows = streams;
       const PoolVariant k = pool_variant(ps, true, false);
-      if (k.any != w.any || k.stream_rows != (streams && w.streams)) ++bad;
+      if (k.kind != w.kind || k.stream_rows != (streams && w.streams)) ++bad;
     }
   }
+  // a run's tile: within 16 KiB, in the general kernels five workgroups of four waves
+  // (twenty of one) a CU with it
+  for (PoolKind kind : {POOL_FAST, POOL_NARROW, POOL_WIDE})
+    for (int waves : {1, 2, 4, 8, 16})
+      for (int dim : {4, 12, 128, 256, 512, 5000}) {
+        ++cases;
+        const int vecs_dim = dim > 512 ? 0 : dim;  // wider rows bypass the tile
+        const int bags = pool_tile_bags(kind, waves, dim, vecs_dim);
+        if (bags < 1 || (bags > 1 && bags * dim > 4096)) ++bad;
+        if (kind != POOL_FAST && bags > 1 && pool_lds_bytes(true, true, waves, bags * vecs_dim) * 20 > (size_t)waves * 160 * 1024) ++bad;
+      }
   // workgroups that fit a CU's 160 KiB: (any, weighted, waves, tile floats) -> at least
   struct Fit { bool any, weighted; int waves, floats, at_least; };
   for (const Fit& f : {Fit{false, true, 16, 2048, 2}, Fit{false, true, 8, 1024, 4}, Fit{false, true, 4, 4096, 4},

@@ -47,23 +47,26 @@ def _inputs(dtype, vecs, L, rows, B, R, C, weighted, seed):
 @pytest.mark.parametrize("mode", ["sum", "weighted", "mean"])
 @pytest.mark.parametrize("kind", ["edges", "slot"])
 @pytest.mark.parametrize("dtype", [synth.F32, synth.F16, synth.BF16])
-def test_any_width(dtype, kind, mode):
+@pytest.mark.parametrize("widest", [130, 32])  # with and without rows of more than 32 vectors
+def test_any_width(widest, dtype, kind, mode):
     import torch
     B, R, C = 42, 2, 21
     rng = np.random.default_rng([2305, 6942, 67, dtype, kind == "slot"])
     L = []
-    for v in VECS:
+    vecs = [v for v in VECS if v <= widest]
+    for v in vecs:
         G = max(1, 64 // v)
         L.append(rng.choice([0, 1, G - 1, G, G + 1, 8 * G - 1, 8 * G, 8 * G + 1], B) if kind == "edges"
-                 else rng.choice([0, 1, 127, 129, 511, 512, 513, 700], B))
-    inp = _inputs(dtype, VECS, np.concatenate(L), 90, B, R, C, mode == "weighted", dtype)
+                 else rng.choice([0, 1, 127, 129, 447, 448, 449, 511, 512, 513, 700], B))
+    inp = _inputs(dtype, vecs, np.concatenate(L), 90, B, R, C, mode == "weighted", dtype)
     w = inp.w
-    say("any tables", dtype, kind, mode)
+    say("any tables", widest, dtype, kind, mode)
     dev = sdev.to_device(inp)
     s64, a64, _ = oracle.pool_inputs(inp, mean=mode == "mean")
     outs = []
     for opts in (dict(), dict(bags_per_run=3, waves_per_wg=1, stream_rows=0, check_indices=1),
-                 dict(bags_per_run=21, persistent_wgs_per_cu=1, release_mode=0), dict(rows_in_flight=4)):
+                 dict(bags_per_run=21, persistent_wgs_per_cu=1, release_mode=0), dict(rows_in_flight=4),
+                 dict(rows_in_flight=16, waves_per_wg=16), dict(bags_per_run=21, waves_per_wg=1)):
         plan = make_plan(w, pooling_mode=int(mode == "mean"), **opts)
         for fused in (True, False):
             send, _, flags = new_buffers(w)

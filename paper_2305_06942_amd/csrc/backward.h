@@ -51,6 +51,16 @@ struct DeliverArgs {
   int32_t per_table;
 };
 
+// LDS words for a weighted run's weights beside its rows_lds bytes of gradient
+// rows and offsets: up to 8 KiB (eight bags of 250 lookups; runs of more read
+// theirs from memory), within the run's 64 KiB, and within 5 KiB a wave, so that
+// they leave a CU its 32 waves.
+inline int32_t backward_weight_slots(int64_t rows_lds, int32_t waves) {
+  const int64_t most = waves < 12 ? 5120 * (int64_t)waves : 65536;
+  const int64_t spare = (most - rows_lds) / 4;
+  return (int32_t)(spare < 0 ? 0 : spare > 2048 ? 2048 : spare);
+}
+
 hipError_t launch_backward(const BackwardArgs& a, int64_t* value_base, int block, size_t lds, hipStream_t stream);
 hipError_t launch_deliver(const DeliverArgs& a, int grid, int block, hipStream_t stream);
 

@@ -629,10 +629,9 @@ int ebag_a2a_backward(ebag_a2a_t h, const float* grad_buf, const uint32_t* grad_
   if (K > block - 1) K = block - 1;
   BackwardArgs a;
   std::memset(&a, 0, sizeof a);
-  // Weighted: 8 KiB for the run's weights (eight bags of 250 lookups); longer
-  // runs read theirs from memory.
-  a.w_slots = weights ? 2048 : 0;
-  const size_t lds = (size_t)K * max_dim * sizeof(float) + (size_t)(K + 1) * sizeof(int64_t) + a.w_slots * sizeof(float);
+  const size_t rows_lds = (size_t)K * max_dim * sizeof(float) + (size_t)(K + 1) * sizeof(int64_t);
+  a.w_slots = weights ? backward_weight_slots((int64_t)rows_lds, h->opts.backward_waves_per_wg) : 0;
+  const size_t lds = rows_lds + a.w_slots * sizeof(float);
   a.grad = grad_buf;
   a.flags = grad_flags;
   a.values = values;

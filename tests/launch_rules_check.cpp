@@ -3,10 +3,11 @@
 // launch constant is exact; the kernels' run decoding (run_at on a RunOrder)
 // is the one on the SliceOrder; which pooling kernel and which loads a plan's
 // tables get; pooling workgroups' LDS leaves a CU the workgroups that their
-// registers allow.
+// registers allow, and a weighted backward's keep to their bounds.
 #include <cstdint>
 #include <cstdio>
 
+#include "backward.h"
 #include "common.h"
 
 int main() {
@@ -97,6 +98,15 @@ int main() {
     ++cases;
     if ((int64_t)pool_lds_bytes(f.any, f.weighted, f.waves, f.floats) * f.at_least > 160 * 1024) ++bad;
   }
+  // a weighted backward's run stays within 64 KiB, and its weights leave a CU its
+  // 32 waves (or what the rows alone leave it)
+  for (int waves : {1, 2, 4, 8, 16})
+    for (int64_t rows_lds : {(int64_t)64, (int64_t)2088, (int64_t)16424, (int64_t)57464, (int64_t)65536}) {
+      ++cases;
+      const int64_t lds = rows_lds + 4 * (int64_t)backward_weight_slots(rows_lds, waves);
+      if (lds > 65536 || (lds > rows_lds && lds * 32 > (int64_t)waves * 160 * 1024)) ++bad;
+      if (waves == 16 && rows_lds < 57344 && lds != rows_lds + 8192) ++bad;
+    }
   std::printf("cases=%d bad=%d\n", cases, bad);
   return bad != 0;
 }

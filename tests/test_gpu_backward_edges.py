@@ -64,6 +64,15 @@ def test_weights_around_their_lds_slots(rows):
     _check([8, 20], [rows, 0, 7, 0, rows - 5, 5] * 2, "weighted", backward_bags_per_run=2)
 
 
+@pytest.mark.parametrize("per_bag", [1, 144, 145, 300])
+@pytest.mark.parametrize("waves", [1, 16])
+def test_weights_beside_rows_that_nearly_fill_lds(waves, per_bag):
+    """Fourteen rows of 1024 floats a run leave 2018 words for its weights (none
+    with one wave)."""
+    say("backward full LDS", waves, per_bag)
+    _check([1024], [per_bag] * 28, "weighted", backward_bags_per_run=16, backward_waves_per_wg=waves)
+
+
 @pytest.mark.parametrize("mode", ["sum", "weighted", "mean"])
 def test_every_bag_empty(mode):
     say("backward empty", mode)

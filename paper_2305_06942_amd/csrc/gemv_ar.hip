@@ -174,6 +174,10 @@ template <int DT, class S>
 __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int hi, const XVec<S>& x,
                              bool device_scope) {
   constexpr int RPI = S::RPI, UJ = S::UJ;
+  // Steps of 64 vectors past the row's end are skipped where a pass takes four or
+  // more of a row (1 x 35253 x 2320 fp32: 63.5 us without, 62.0 us; 2 x 30000 x 3000
+  // bf16: 66.0 and 64.5; and with four whole steps, 4 x 65536 x 2048 bf16, 173 and 167).
+  constexpr bool SKIPS = !S::XREG || RPI == 4;
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
@@ -205,6 +209,7 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
           const int v = v0 + u * 64 + l;
+          if (SKIPS && v0 + u * 64 >= V) continue;  // no lane has one
           const uint32_t off = v < V ? (uint32_t)(v * 16 + g * (int)row_bytes) : 0x80000000u;  // past any row
 #pragma unroll
           for (int j = 0; j < RPI; ++j)
@@ -213,10 +218,11 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
           const int v = v0 + u * 64 + l;
-          if (S::XREG || v < V) {
+          if (S::XREG ? !SKIPS || v0 + u * 64 < V : v < V) {
             u4v xv = x.at(u, v);
-            // bf16: widened here, not kept widened (twice the registers)
-            if (DT == 2) asm volatile("" : "+v"(xv));
+            // widened here, not kept widened (twice the registers: fp16, 1 x 35253 x
+            // 1160, 28.9 us kept, 23.1 us like this)
+            if (DT == 2 || (DT == 1 && S::XREG && RPI == 4)) asm volatile("" : "+v"(xv));
 #pragma unroll
             for (int j = 0; j < RPI; ++j) acc[j] += dot16<DT>(ra[j][u], xv);
           }

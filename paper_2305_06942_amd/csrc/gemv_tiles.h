@@ -28,14 +28,14 @@ __host__ __device__ inline uint32_t first_tile(const TileOwners& o, int q, uint3
   return o.own[q] + (p < m ? p + P - m : p - m);
 }
 
-// Workgroups a tile's rows are split over: about kTargetWaves wavefronts in all
+// Workgroups a tile's rows are split over: up to kTargetWaves wavefronts in all
 // `wgs` workgroups of W waves, each with at least one row and 4 KiB of the matrix
-// per tile.  At 2048 waves of 16 KiB in flight the device has 32 MiB on the way;
-// more of them (4096, 8192) were no faster and at 1 x 4096 x 4096 bf16 slower
-// (17.0, 23.6, 23.3 us; unsplit 36.7), fewer leave small M idle: 1 x 3233 x 8096
-// fp32 (51 tiles) took 92 us unsplit and takes 28 us, 1 x 256 x 8192 fp32 82 us
-// and 15 us.
-constexpr int64_t kTargetWaves = 2048;
+// per tile.  Few waves leave small M idle: 1 x 3233 x 8096 fp32 (51 tiles) took 92
+// us unsplit and takes 28 us, 1 x 16384 x 4096 fp16 (512 waves) 40.6 and 29.7.  1024
+// waves of 16 KiB in flight are enough: at 2 x 16384 x 4096 fp16 split in two, each
+// half staging x again, 53.4 us, whole 50.5 us.  More in all (4096, 8192) were no
+// faster and at 1 x 4096 x 4096 bf16 slower (17.0 us at 2048, 23.6, 23.3).
+constexpr int64_t kTargetWaves = 1536;
 inline int32_t split_for(int64_t wgs, int32_t W, int32_t TM, int64_t row_bytes, int32_t* sub_rows) {
   const int64_t min_rows = row_bytes >= 4096 ? 1 : 4096 / row_bytes;
   int64_t split = kTargetWaves / (wgs * W);

@@ -33,7 +33,7 @@ KERNEL_SOURCES = {
     "fused_pool_kernel": ["paper_2305_06942_amd/csrc/pool_kernels.h", "paper_2305_06942_amd/csrc/common.h"],
     "backward_kernel": ["paper_2305_06942_amd/csrc/backward.hip", "paper_2305_06942_amd/csrc/backward.h",
                         "paper_2305_06942_amd/csrc/common.h"],
-    "gemv_ar_last_arriver_kernel": ["paper_2305_06942_amd/csrc/gemv_ar.hip"],
+    "gemv_ar_last_arriver_kernel": ["paper_2305_06942_amd/csrc/gemv_ar.hip", "paper_2305_06942_amd/csrc/gemv_tiles.h"],
 }
 # GEMV + AllReduce records are keyed by the output size: workload "m<M>".
 TRAFFIC_FILE = {"fused_pool_kernel": "traffic_{}.json", "backward_kernel": "traffic_backward_{}.json",

@@ -105,7 +105,9 @@ typedef struct ebag_a2a_opts {
   int32_t waves_per_wg;        /* wavefronts (64 lanes) per pooling workgroup, 1..16 (default 4) */
   int32_t bags_per_run;        /* bags a workgroup pools before one slice-counter update (default 16;
                                   capped so that the run's pooled rows, bags x max D floats, fit a 16 KiB
-                                  LDS tile, and at chunk_samples) */
+                                  LDS tile -- 4.5 KiB a wave where that is less, in plans with check_indices,
+                                  a table of 4 GiB or more or rows that are not 2^k <= 64 sixteen-byte
+                                  vectors -- and at chunk_samples) */
   int32_t rows_in_flight;      /* 16-byte row loads each wave keeps in flight: 4, 8 or 16 (default 8) */
   int32_t persistent_wgs_per_cu; /* 0: one workgroup per run; >0: persistent grid of that many WGs per CU
                                     (-1: as many as fit), whose workgroups claim runs in production order
@@ -131,7 +133,8 @@ typedef struct ebag_a2a_opts {
                                   1: a flag per (destination, C samples, table) -- the paper's per-table
                                   slice (Sec. III-A); see "Slices" above */
   int32_t backward_bags_per_run;  /* ebag_a2a_backward: bags per workgroup (default 4; capped so that the
-                                     bags' gradient rows fit in 64 KiB of LDS) */
+                                     bags' gradient rows and offsets fit in 64 KiB of LDS; the bags'
+                                     weights take up to 8 KiB of what they leave) */
   int32_t backward_waves_per_wg;  /* ebag_a2a_backward: wavefronts per workgroup, 1..16 (default 16) */
   int32_t table_major;         /* 0 (default): runs slice by slice, tables fastest inside a slice; 1: table
                                   by table, slices in order inside each table, and (when T is a multiple
@@ -168,8 +171,10 @@ int ebag_a2a_default_opts(ebag_a2a_opts_t* opts);
  *   max_batch: largest B any forward will use (sizes the slice counters and
  *     the unfused scratch of max_batch * sum(D) floats).
  *   max_ranks: largest R any forward will use.
- * Device memory owned by the plan: slice counters, unfused scratch, table
- * descriptors, status word, trace buffers; released by ebag_a2a_destroy.
+ * Device memory owned by the plan: slice counters (whole slices: 256 bytes
+ * each as long as that is at most 64 MiB in all, else less; per-table slices: 4
+ * bytes each), unfused scratch, table descriptors, status word, trace buffers;
+ * released by ebag_a2a_destroy.
  */
 int ebag_a2a_create(ebag_a2a_t* out, int32_t num_tables, const int64_t* rows_per_table,
                     const int32_t* dim_per_table, int32_t table_dtype, int32_t chunk_samples,

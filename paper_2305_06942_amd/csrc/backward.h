@@ -24,7 +24,6 @@ struct BackwardArgs {
   int32_t T;
   int32_t C;
   int32_t K;
-  int32_t J;
   int32_t sum_dim;
   int32_t max_dim;
   int32_t per_table;

@@ -143,7 +143,6 @@ struct PoolArgs {
   int32_t T;
   int32_t C;
   int32_t K;                  // bags per run
-  int32_t J;                  // runs per (slice, table) = ceil(C / K)
   int32_t sum_dim;
   int32_t check;              // check offsets / indices
   int32_t release_mode;       // 0 agent-scope release fence, 1 device-scope stores + completion wait
@@ -178,8 +177,8 @@ struct PoolSetup {
 // Which of the pooling kernels a launch takes.  POOL_FAST: every table below 4
 // GiB (32-bit offsets) with rows of 2^k <= 64 sixteen-byte vectors, no index
 // report; its kernel needs fewer registers (fp32: 59 instead of 69 and 82) and
-// reads such tables faster (26 tables x 16384 bags of 0 to 3 rows of 512 bytes: 113
-// us, against 158 us by the general one).  POOL_NARROW, POOL_WIDE: the general
+// reads such tables faster (26 tables x 16384 bags of 0 to 3 rows of 512 bytes: 110
+// us, against 143 us by the general one).  POOL_NARROW, POOL_WIDE: the general
 // kernel for any tables and for index reports, without and with rows of more than
 // 32 vectors, whose code costs the others registers.
 enum PoolKind { POOL_FAST = 0, POOL_NARROW = 1, POOL_WIDE = 2 };
@@ -193,6 +192,9 @@ typedef void (*pool_fn)(const PoolArgs);
 pool_fn pick_pool_f32(const PoolVariant& k);
 pool_fn pick_pool_f16(const PoolVariant& k);
 pool_fn pick_pool_bf16(const PoolVariant& k);
+pool_fn pick_pool_wide_f32(const PoolVariant& k);
+pool_fn pick_pool_wide_f16(const PoolVariant& k);
+pool_fn pick_pool_wide_bf16(const PoolVariant& k);
 
 // stream_rows: the general kernel takes it only where every table's rows are
 // whole 128-byte lines.  A line that two rows share is read again soon, and loaded

@@ -307,13 +307,13 @@ void ebag::fill_pool_args(const PoolSetup& s, const int32_t* indices, const int6
   a->ticket = s.d_ticket;
   a->B = B;
   a->K = K;
-  a->J = (s.C + K - 1) / K;
   a->T = s.T;
   a->C = s.C;
-  a->nruns = so.n_chunks * (int64_t)s.T * a->J;
+  const int32_t J = (s.C + K - 1) / K;
+  a->nruns = so.n_chunks * (int64_t)s.T * J;
   a->suppress = o.debug_suppress_flag;
   a->so = so;
-  a->ro = make_run_order(so, s.T, a->J);
+  a->ro = make_run_order(so, s.T, J);
   a->by_waves = make_divisor(o.waves_per_wg);
   a->sum_dim = s.sum_dim;
   a->check = o.check_indices;
@@ -620,8 +620,8 @@ int ebag_a2a_backward(ebag_a2a_t h, const float* grad_buf, const uint32_t* grad_
   int32_t max_dim = 0;
   for (const TabMeta& m : h->meta) max_dim = m.dim > max_dim ? m.dim : max_dim;
   const int block = 64 * h->opts.backward_waves_per_wg;
-  // LDS holds the run's K gradient rows and K + 1 offsets: K is capped so
-  // that they fit in 64 KiB.
+  // LDS holds the run's K gradient rows, K + 1 offsets and what fits of its
+  // weights: K is capped so that the first two fit in 64 KiB.
   int32_t K = h->opts.backward_bags_per_run < h->C ? h->opts.backward_bags_per_run : h->C;
   const int32_t k_fit = (int32_t)(65536 / ((size_t)max_dim * sizeof(float) + sizeof(int64_t)) - 1);
   if (k_fit < 1) return fail(EBAG_EUNSUPPORTED, "backward: rows of %d floats do not fit in LDS", max_dim);
@@ -647,10 +647,10 @@ int ebag_a2a_backward(ebag_a2a_t h, const float* grad_buf, const uint32_t* grad_
   a.T = h->T;
   a.C = h->C;
   a.K = K;
-  a.J = (h->C + a.K - 1) / a.K;
-  a.nruns = so.n_chunks * (int64_t)h->T * a.J;
+  const int32_t J = (h->C + a.K - 1) / a.K;
+  a.nruns = so.n_chunks * (int64_t)h->T * J;
   if (a.nruns >= INT_MAX) return fail(EBAG_EINVAL, "too many runs (%lld) for one launch", (long long)a.nruns);
-  a.ro = make_run_order(so, h->T, a.J);
+  a.ro = make_run_order(so, h->T, J);
   a.sum_dim = h->sum_dim;
   a.max_dim = max_dim;
   a.per_table = h->opts.slice_granule == 1;

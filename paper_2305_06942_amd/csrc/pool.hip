@@ -5,10 +5,11 @@ namespace ebag {
 namespace {
 
 pool_fn pick(const PoolVariant& k) {
+  const bool wide = k.kind == POOL_WIDE;
   switch (k.dtype) {
-    case 1: return pick_pool_f16(k);
-    case 2: return pick_pool_bf16(k);
-    default: return pick_pool_f32(k);
+    case 1: return wide ? pick_pool_wide_f16(k) : pick_pool_f16(k);
+    case 2: return wide ? pick_pool_wide_bf16(k) : pick_pool_bf16(k);
+    default: return wide ? pick_pool_wide_f32(k) : pick_pool_f32(k);
   }
 }
 

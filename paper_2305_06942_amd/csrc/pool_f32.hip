@@ -3,6 +3,8 @@
 
 namespace ebag {
 
-pool_fn pick_pool_f32(const PoolVariant& k) { return pick_u<EF32>(k); }
+pool_fn pick_pool_f32(const PoolVariant& k) {
+  return k.kind == POOL_FAST ? pick_u<EF32, POOL_FAST>(k) : pick_u<EF32, POOL_NARROW>(k);
+}
 
 }  // namespace ebag

@@ -1,6 +1,6 @@
 // Embedding-bag pooling kernels for gfx950.  Templates over the storage type;
-// each type's kernels are instantiated in a source file of their own
-// (pool_f32.hip, pool_f16.hip, pool_bf16.hip), which compile side by side.
+// each type's kernels are instantiated in source files of their own (pool_f32.hip,
+// pool_wide_f32.hip, ...), which compile side by side.
 //
 // One wavefront pools whole bags (the paper's "logical workgroup" of the
 // EmbeddingBag kernel, Sec. III-A), a contiguous block of them.  A workgroup
@@ -908,18 +908,17 @@ pool_fn pick_n(const PoolVariant& k) {
   return k.stream_rows ? pick_f<E, U, WT, true, KIND>(k) : pick_f<E, U, WT, false, KIND>(k);
 }
 
-template <class E, int U, bool WT>
-pool_fn pick_t(const PoolVariant& k) {
-  return k.kind == POOL_FAST ? pick_n<E, U, WT, POOL_FAST>(k)
-         : k.kind == POOL_NARROW ? pick_n<E, U, WT, POOL_NARROW>(k) : pick_n<E, U, WT, POOL_WIDE>(k);
+template <class E, int U, int KIND>
+pool_fn pick_w(const PoolVariant& k) {
+  return k.weighted ? pick_n<E, U, true, KIND>(k) : pick_n<E, U, false, KIND>(k);
 }
 
-template <class E>
+template <class E, int KIND>
 pool_fn pick_u(const PoolVariant& k) {
   switch (k.rows_in_flight) {
-    case 4: return k.weighted ? pick_t<E, 4, true>(k) : pick_t<E, 4, false>(k);
-    case 16: return k.weighted ? pick_t<E, 16, true>(k) : pick_t<E, 16, false>(k);
-    default: return k.weighted ? pick_t<E, 8, true>(k) : pick_t<E, 8, false>(k);
+    case 4: return pick_w<E, 4, KIND>(k);
+    case 16: return pick_w<E, 16, KIND>(k);
+    default: return pick_w<E, 8, KIND>(k);
   }
 }
 

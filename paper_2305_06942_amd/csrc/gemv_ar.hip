@@ -39,6 +39,7 @@ namespace {
 
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 constexpr int kInFlight = 16;      // 16-byte loads in flight per lane
+constexpr int kBf16Rows = -8;      // eight rows at once, one vector of each (bf16)
 constexpr int kMaxXBytes = 64 * 1024;
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
@@ -127,10 +128,10 @@ __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0
 
 // How a launch shapes the GEMV: RPI rows at once, the lane's vectors of x in
 // registers (XREG: rows of at most 64 * UJ vectors) or in LDS.
-template <int RPI_, bool XREG_>
+template <int RPI_, bool XREG_, int UJ_ = kInFlight / RPI_>
 struct Shape {
   static constexpr int RPI = RPI_;
-  static constexpr int UJ = kInFlight / RPI_;
+  static constexpr int UJ = UJ_;
   static constexpr bool XREG = XREG_;
 };
 
@@ -419,6 +420,8 @@ gemv_fn pick_kernel(int which) {
 template <int DT>
 gemv_fn pick_shape(int which, int rpi, bool xreg) {
   if (xreg) {
+    if constexpr (DT == 2)
+      if (rpi == kBf16Rows) return pick_kernel<DT, Shape<8, true, 1>>(which);
     switch (rpi) {
       case 16: return pick_kernel<DT, Shape<16, true>>(which);
       case 8: return pick_kernel<DT, Shape<8, true>>(which);
@@ -531,10 +534,14 @@ int note_forward(gemv_ar_plan* h, hipStream_t stream) {
 // vectors, x in LDS) and now: 4 ranks x 30000 x 96 bf16 32.8 us and 20.7 us; 8
 // x 8192 x 1024 fp16 33.5 and 28.9; 4 x 65536 x 2048 fp16 (4 rows x 4 vectors
 // still, x in registers) 165.9 and 164.8, 6.5 TB/s, the streaming read ceiling.
+// bf16 rows of 33 to 64 vectors go eight at once, one vector a lane of each: sixteen
+// take 117 registers for them and their sums (1 x 60000 x 512: 21.1 us, 16.8 us like
+// this, 20.0 us four rows at once with x in LDS).
 void launch_shape(gemv_ar_plan* h) {
   const int64_t V = h->max_x_bytes / 16;
   h->xreg = V <= 256;
   h->rpi = V <= 64 ? 16 : V <= 128 ? 8 : 4;
+  if (h->dtype == EBAG_BF16 && V > 32 && V <= 64) h->rpi = kBf16Rows;
   h->lanes = 64;
   while (h->lanes > 1 && V <= h->lanes / 2) h->lanes /= 2;
   // Long rows, fewer than four of them for each of 2048 waves: fewer rows at

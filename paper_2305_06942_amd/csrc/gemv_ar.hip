@@ -40,6 +40,7 @@ namespace {
 constexpr int kBufferWord3 = 0x00020000;  // raw buffer, 32-bit data format
 constexpr int kInFlight = 16;      // 16-byte loads in flight per lane
 constexpr int kBf16Rows = -8;      // eight rows at once, one vector of each (bf16)
+constexpr int kWholeRows = -4;     // four rows at once, all four vectors of each (fp16)
 constexpr int kMaxXBytes = 64 * 1024;
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
@@ -128,8 +129,9 @@ __device__ __forceinline__ void wait_all_memory() { __builtin_amdgcn_s_waitcnt(0
 
 // How a launch shapes the GEMV: RPI rows at once, the lane's vectors of x in
 // registers (XREG: rows of at most 64 * UJ vectors) or in LDS.
-template <int RPI_, bool XREG_, int UJ_ = kInFlight / RPI_>
+template <int RPI_, bool XREG_, int UJ_ = kInFlight / RPI_, bool TRIM_ = !XREG_ || RPI_ == 4>
 struct Shape {
+  static constexpr bool TRIM = TRIM_;  // steps of 64 vectors past the row's end are skipped
   static constexpr int RPI = RPI_;
   static constexpr int UJ = UJ_;
   static constexpr bool XREG = XREG_;
@@ -175,10 +177,10 @@ template <int DT, class S>
 __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int hi, const XVec<S>& x,
                              bool device_scope) {
   constexpr int RPI = S::RPI, UJ = S::UJ;
-  // Steps of 64 vectors past the row's end are skipped where a pass takes four or
-  // more of a row (1 x 35253 x 2320 fp32: 63.5 us without, 62.0 us; 2 x 30000 x 3000
-  // bf16: 66.0 and 64.5; and with four whole steps, 4 x 65536 x 2048 bf16, 173 and 167).
-  constexpr bool SKIPS = !S::XREG || RPI == 4;
+  // TRIM, where a pass takes four or more of a row: 1 x 35253 x 2320 fp32 63.5 us
+  // without, 62.0 us; 2 x 30000 x 3000 bf16 66.0 and 64.5; and with four whole steps,
+  // 4 x 65536 x 2048, bf16 172 to 175 and 167 to 172, but fp16 166.5 and 170, so not
+  // there.
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
@@ -210,7 +212,7 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
           const int v = v0 + u * 64 + l;
-          if (SKIPS && v0 + u * 64 >= V) continue;  // no lane has one
+          if (S::TRIM && v0 + u * 64 >= V) continue;  // no lane has one
           const uint32_t off = v < V ? (uint32_t)(v * 16 + g * (int)row_bytes) : 0x80000000u;  // past any row
 #pragma unroll
           for (int j = 0; j < RPI; ++j)
@@ -219,11 +221,11 @@ __device__ void partial_tile(const GemvArgs& a, int r, int64_t tile, int lo, int
 #pragma unroll
         for (int u = 0; u < UJ; ++u) {
           const int v = v0 + u * 64 + l;
-          if (S::XREG ? !SKIPS || v0 + u * 64 < V : v < V) {
+          if (S::XREG ? !S::TRIM || v0 + u * 64 < V : v < V) {
             u4v xv = x.at(u, v);
             // widened here, not kept widened (twice the registers: fp16, 1 x 35253 x
             // 1160, 28.9 us kept, 23.1 us like this)
-            if (DT == 2 || (DT == 1 && S::XREG && RPI == 4)) asm volatile("" : "+v"(xv));
+            if (DT == 2 || (DT == 1 && S::XREG && S::TRIM)) asm volatile("" : "+v"(xv));
 #pragma unroll
             for (int j = 0; j < RPI; ++j) acc[j] += dot16<DT>(ra[j][u], xv);
           }
@@ -420,6 +422,8 @@ gemv_fn pick_kernel(int which) {
 template <int DT>
 gemv_fn pick_shape(int which, int rpi, bool xreg) {
   if (xreg) {
+    if constexpr (DT == 1)
+      if (rpi == kWholeRows) return pick_kernel<DT, Shape<4, true, 4, false>>(which);
     if constexpr (DT == 2)
       if (rpi == kBf16Rows) return pick_kernel<DT, Shape<8, true, 1>>(which);
     switch (rpi) {
@@ -542,6 +546,7 @@ void launch_shape(gemv_ar_plan* h) {
   h->xreg = V <= 256;
   h->rpi = V <= 64 ? 16 : V <= 128 ? 8 : 4;
   if (h->dtype == EBAG_BF16 && V > 32 && V <= 64) h->rpi = kBf16Rows;
+  if (h->dtype == EBAG_F16 && V == 256) h->rpi = kWholeRows;
   h->lanes = 64;
   while (h->lanes > 1 && V <= h->lanes / 2) h->lanes /= 2;
   // Long rows, fewer than four of them for each of 2048 waves: fewer rows at
